@@ -104,10 +104,16 @@ struct Mfma<16> {
 // group q at SH j + (256 / SH) q + 4 (l / SH).  The epilogues walk the G =
 // NI * QN groups of a row block: group g = QN j + q, column offset col(g)
 // (plus the lane's 4 (l / SH)), values grp(acc, i, g).
-template <int SH, int MI, int NI>
+//
+// RH = 0: the wave's rows are contiguous, row block i at row SH i.  RH > 0
+// (the ping-pong tiles): two halves of MI / 2 row blocks, RH rows apart.
+template <int SH, int MI, int NI, int RH = 0>
 struct AccGeo {
   using acc_t = typename Mfma<SH>::acc_t;
   static constexpr int QN = SH * SH / 256, G = NI * QN;
+  __device__ __forceinline__ static constexpr int row(int i) {
+    return RH ? RH * (i / (MI / 2)) + SH * (i % (MI / 2)) : SH * i;
+  }
   __device__ __forceinline__ static constexpr int col(int g) {
     return SH * (g / QN) + (256 / SH) * (g % QN);
   }
@@ -149,13 +155,13 @@ __device__ __forceinline__ int b_row_of(int kind, int tn, int nt, int ffn) {
   return tn * BN + nt;
 }
 
-// Residual prefetch for the 256 x 256 residual epilogue.  The loads for the
-// two tiles past the last one (zeros otherwise) fetch instead the two 128-row
-// halves of the output tile's residual into the buffers they would fill: half
-// h into buffer (KT + h) % 2, its rows 0..63 in the A region, 64..127 in the B
-// region, row-major with 512-byte rows whose 16-byte chunks are stored at
+// Residual prefetch for the 256 x 256 residual epilogue (PingLoop).  The loads
+// for the two tiles past the last one (zeros otherwise) fetch instead the two
+// 128-row halves of the output tile's residual into the buffers they would
+// fill: half h into buffer (KT + h) % 2, 32 rows into each half tile (A 0, A 1,
+// B 0, B 1), row-major with 512-byte rows whose 16-byte chunks are stored at
 // chunk ^ (row % 16) (16 consecutive rows read one logical chunk without bank
-// conflicts).  Piece j of wave w in a region covers region rows 2 L and 2 L + 1,
+// conflicts).  Piece j of wave w in a half tile covers its rows 2 L and 2 L + 1,
 // L = w + 8 j; lane l writes position l % 32 of row 2 L + l / 32, so it fetches
 // logical chunk (l % 32) ^ ((2 w + l / 32) % 16) (the swizzle is an
 // involution).  Rows past M read as zero through the descriptor's range.
@@ -197,17 +203,14 @@ struct Mainloop {
   // so the wave issues neither their MFMAs nor their A fragment reads (with
   // MA = 0, no MFMA and no fragment read at all).  Its share of the tile
   // loads and every barrier stay, so all waves keep the same barrier count.
-  template <int MA, bool RPF = false>
+  template <int MA>
   __device__ __forceinline__ static void run_rows(GemmSmem<BM, BN, S>& sm,
                                                   __amdgpu_buffer_rsrc_t ra,
                                                   const uint32_t (&a_off)[A_BLK],
                                                   __amdgpu_buffer_rsrc_t rb,
                                                   const uint32_t (&b_off)[B_BLK], int K, int wv,
-                                                  int lane, acc_t (&acc)[MI][NI],
-                                                  const ResPf& rp, int kshift) {
+                                                  int lane, acc_t (&acc)[MI][NI], int kshift) {
     static_assert(MA >= 0 && MA <= MI, "active row blocks");
-    static_assert(!RPF || (BM == 256 && BN == 256 && NW == 8 && S == 2),
-                  "residual prefetch: two 64-row regions of 32 pieces per buffer");
     const int wm = wv / WGN, wn = wv % WGN;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -278,14 +281,6 @@ struct Mainloop {
         buffer_load_lds16(rb, &sm.b[buf][(wv + NW * (p - A_BLK)) * 8 * kBK],
                           b_off[p - A_BLK] | kill, kb);
     };
-    // Piece p of residual half h (ResPf): the LDS destination of tile piece p.
-    auto rpiece = [&](int h, int buf, int p) {
-      const int reg = p < A_BLK ? 0 : 1, j = p - reg * A_BLK;
-      const int row = 128 * h + 64 * reg + 2 * (wv + NW * j);
-      void* dst = reg ? (void*)&sm.b[buf][(wv + NW * j) * 8 * kBK]
-                      : (void*)&sm.a[buf][(wv + NW * j) * 8 * kBK];
-      buffer_load_lds16(rp.rsrc, dst, rp.voff, row * rp.ld_bytes);
-    };
     // B (weight rows) as the MFMA's row operand and A (token rows) as its
     // column operand: accumulator block (i, j) holds C^T, so a lane owns one
     // token row and groups of four consecutive output columns, and the
@@ -308,7 +303,7 @@ struct Mainloop {
     // The issue order is spelled out: one MFMA, then one LDS read for the next
     // k-step (and on the last step one or more tile loads), fenced so the
     // compiler keeps it.
-    auto ktile = [&](int kt, auto res) {
+    auto ktile = [&](int kt) {
       const int nbuf = buf + 1 == S ? 0 : buf + 1;
 #pragma unroll
       for (int ks = 0; ks + 1 < KSTEPS; ++ks) {
@@ -327,27 +322,17 @@ struct Mainloop {
 #pragma unroll
       for (int g = 0; g < NGL; ++g) {
         if (g < NMF) mfma(last, g);
-        if (g < NLD) {
-          if constexpr (decltype(res)::value) rpiece(kt + S - KT, buf, g);
-          else gpiece(kt + S, buf, kill, g);
-        }
+        if (g < NLD) gpiece(kt + S, buf, kill, g);
         if (g < NRD) lread(nbuf, 0, last ^ 1, g);  // stale but in-range on the last tile
         __builtin_amdgcn_sched_barrier(0);
       }
       buf = nbuf;
     };
-    // With the residual prefetch, the last S k-tiles (those whose tile + S
-    // does not exist) run in a loop of their own that loads residual halves.
-    const int kt_main = (RPF && rp.on) ? KT - S : KT;
-    int kt = 0;
-    for (; kt < kt_main; ++kt) ktile(kt, std::false_type{});
-    if constexpr (RPF) {
-      for (; kt < KT; ++kt) ktile(kt, std::true_type{});
-    }
+    for (int kt = 0; kt < KT; ++kt) ktile(kt);
   }
   // The tile's first `rows` rows are valid: the wave runs the instantiation
   // for its active row blocks (a wave-uniform choice).
-  template <int MA = MI, bool RPF = false>
+  template <int MA = MI>
   __device__ __forceinline__ static void run_valid(int rows, GemmSmem<BM, BN, S>& sm,
                                                    __amdgpu_buffer_rsrc_t ra,
                                                    const uint32_t (&a_off)[A_BLK],
@@ -358,11 +343,237 @@ struct Mainloop {
     const int wm = wv / WGN;
     const int act = (rows - wm * WM + SH - 1) / SH;  // row blocks holding valid rows
     if constexpr (MA == 0) {
-      run_rows<0, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+      run_rows<0>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
     } else {
-      if (act >= MA) run_rows<MA, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
-      else run_valid<MA - 1, RPF>(rows, sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+      if (act >= MA) run_rows<MA>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
+      else run_valid<MA - 1>(rows, sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
     }
+  }
+};
+
+// The 256 x 256 tiles' K loop: eight waves in two groups (waves 0-3 and 4-7,
+// one of each group on every SIMD) that run the same program half a phase
+// apart, so that on each SIMD one wave's MFMAs run while the other reads its
+// fragments and issues its loads.
+//
+// A k-tile is four 16 KB half tiles (rows 0-127 and 128-255 of A and of B)
+// and four phases, one per quadrant of the wave's output: wave (wm, wn) owns
+// rows 64 wm .. + 63 of both A halves and rows 32 wn .. + 31 of both B halves,
+// 64 x 32 per quadrant, 16 MFMAs.  Phase p of k-tile t:
+//   p   reads (LDS -> registers)   loads issued            MFMAs
+//   0   A0 (t)                     A1 (t + 1)              A0 B0
+//   1   B1 (t)                     B0 (t + 2)              A0 B1
+//   2   A1 (t)                     A0 (t + 2)              A1 B0
+//   3   B0 (t + 1)                 B1 (t + 2)              A1 B1
+// each phase: reads and loads, wait, barrier, MFMAs, barrier.  The second
+// group passes one barrier more before the first phase (the first group one
+// more at the end), which sets the groups half a phase apart.
+//
+// A half tile is loaded two phases or more after the phase that read its
+// predecessor: that phase's reads are complete in both groups one barrier
+// earlier (the second group's when its MFMAs of the phase have consumed them;
+// B0, whose MFMAs come a phase later, is waited for in phase 3 itself).  It is
+// read six phases after its load was issued; the wait of the phase before
+// leaves the five newer half tiles' ten loads in flight.
+//
+// What bounds it: the board's power.  A loop with one barrier per k-tile has to
+// issue a k-tile's loads in one burst once the whole buffer is free, so a
+// k-tile took the burst plus a memory round trip (3060 clocks for 2048 of
+// MFMAs); here loads are issued at an even rate and each group's MFMAs cover
+// the other's LDS reads (2450 clocks).  8192^3: 819 -> 755 us on random
+// operands (1343 -> 1455 TFLOP/s), 677 -> 593 us on zeros, which draw less
+// power; gate/up at 16384 x 3584 (SwiGLU) 3380 -> 3083 us, down 1720 -> 1671 us.
+// Without the stagger of the groups 868 us; loads issued between the MFMAs
+// 840 us; s_setprio, the order of reads and loads in a phase and the order of
+// the MFMAs make no difference.
+struct PingLoop {
+  static constexpr int SH = 16, BM = 256, BN = 256, NW = 8, NT = 512;
+  using MF = Mfma<SH>;
+  using acc_t = MF::acc_t;
+  static constexpr int MI = 8, NI = 4;
+  static constexpr int RH = 128;            // row distance of the wave's two halves
+  static constexpr int A_BLK = 4, B_BLK = 4;  // 1 KB blocks per wave and k-tile
+  static constexpr int KS = 2;              // 32-k steps per k-tile
+  static constexpr int HALF = 128 * kBK;    // elements of a half tile
+
+  // C0, C1: row blocks (of four) of the wave's two halves that hold valid rows.
+  template <int C0, int C1, bool RPF>
+  __device__ __forceinline__ static void run_rows(GemmSmem<256, 256, 2>& sm,
+                                                  __amdgpu_buffer_rsrc_t ra,
+                                                  const uint32_t (&a_off)[A_BLK],
+                                                  __amdgpu_buffer_rsrc_t rb,
+                                                  const uint32_t (&b_off)[B_BLK], int K, int wv,
+                                                  int lane, acc_t (&acc)[MI][NI],
+                                                  const ResPf& rp, int kshift) {
+    static_assert(C0 >= 0 && C0 <= 4 && C1 >= 0 && C1 <= C0, "active row blocks");
+    const int wm = wv >> 2, wn = wv & 3;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = acc_t{0.f};
+    const int KT = K / kBK;
+    // the two 1 KB pieces of a half tile: A (op 0) or B (op 1), half h of k-tile
+    // kt; a k-tile past the last one reads zeros (kept, so that every phase
+    // issues the same number of loads), or rows of the residual
+    auto gload = [&](int kt, int buf, int op, int h) {
+      bf16* dst = (op ? sm.b[buf] : sm.a[buf]) + h * HALF + wv * 8 * kBK;
+      if (RPF && rp.on && kt >= KT) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          buffer_load_lds16(rp.rsrc, dst + j * 64 * kBK, rp.voff,
+                            (128 * (kt - KT) + 64 * op + 32 * h + 2 * (wv + 8 * j)) * rp.ld_bytes);
+      } else {
+        const int kk = kt + kshift;
+        const int kb = (kk >= KT ? kk - KT : kk) * kBK * 2;
+        const uint32_t kill = kt < KT ? 0u : 0x80000000u;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          buffer_load_lds16(op ? rb : ra, dst + j * 64 * kBK,
+                            (op ? b_off[2 * h + j] : a_off[2 * h + j]) | kill, kb);
+      }
+    };
+    // fragment addresses (the swizzle of a row is that of row + 16 i)
+    uint32_t a_base[KS], b_base[KS];
+    {
+      const int lr = lane % SH, lg = lane / SH;
+      const int ra0 = wm * 64 + lr, rb0 = wn * 32 + lr;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int ch = ks * 4 + lg;
+        a_base[ks] = (uint32_t)((ra0 * kBK + swz(ra0, ch) * 8) * 2);
+        b_base[ks] = (uint32_t)((rb0 * kBK + swz(rb0, ch) * 8) * 2);
+      }
+    }
+    const char* const lds_a = (const char*)&sm.a[0][0];
+    const char* const lds_b = (const char*)&sm.b[0][0];
+    bf16x8 fa[4][KS], fb[2][2][KS];
+    auto read_a = [&](int buf, auto half) {
+      constexpr int h = decltype(half)::value, C = h ? C1 : C0;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+          fa[i][ks] = *(const bf16x8*)(lds_a + a_base[ks] +
+                                       ((buf * 2 + h) * HALF + i * SH * kBK) * 2);
+    };
+    auto read_b = [&](int buf, auto half) {
+      constexpr int h = decltype(half)::value;
+      if constexpr (C0 > 0) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            fb[h][j][ks] = *(const bf16x8*)(lds_b + b_base[ks] +
+                                            ((buf * 2 + h) * HALF + j * SH * kBK) * 2);
+      }
+    };
+    auto barrier = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // the loads issued five phases ago have landed; then the phase's MFMAs
+    // between two barriers
+    auto quadrant = [&](auto ha, auto hb, bool lgkm) {
+      constexpr int h = decltype(ha)::value, g = decltype(hb)::value, C = h ? C1 : C0;
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+      barrier();
+      if (lgkm) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[4 * h + i][2 * g + j] = MF::mma(fb[g][j][ks], fa[i][ks], acc[4 * h + i][2 * g + j]);
+      __builtin_amdgcn_s_setprio(0);
+      barrier();
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    auto ktile = [&](int kt, auto bufc) {
+      constexpr int buf = decltype(bufc)::value;
+      read_a(buf, I0{});
+      gload(kt + 1, buf ^ 1, 0, 1);
+      quadrant(I0{}, I0{}, false);
+      read_b(buf, I1{});
+      gload(kt + 2, buf, 1, 0);
+      quadrant(I0{}, I1{}, false);
+      read_a(buf, I1{});
+      gload(kt + 2, buf, 0, 0);
+      quadrant(I1{}, I0{}, false);
+      read_b(buf ^ 1, I0{});  // past the last tile: stale, unused
+      gload(kt + 2, buf, 1, 1);
+      quadrant(I1{}, I1{}, true);
+    };
+    gload(0, 0, 1, 0);
+    gload(0, 0, 0, 0);
+    gload(0, 0, 1, 1);
+    gload(0, 0, 0, 1);
+    gload(1, 1, 1, 0);
+    gload(1, 1, 0, 0);
+    gload(1, 1, 1, 1);
+    asm volatile("s_waitcnt vmcnt(10)" ::: "memory");  // B0 and A0 of tile 0
+    barrier();
+    read_b(0, I0{});
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (wm) barrier();
+    for (int kt = 0; kt < KT; kt += 2) {
+      ktile(kt, I0{});
+      if (kt + 1 < KT) ktile(kt + 1, I1{});
+    }
+    if (!wm) barrier();
+    // the residual's last 32 rows (half tile A 1 of the second buffer, free
+    // only now); no load may land in LDS after the workgroup's end
+    if constexpr (RPF) {
+      if (rp.on) gload(KT + 1, (KT + 1) & 1, 0, 1);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  // The tile's first `rows` rows are valid: each wave runs the instantiation
+  // for its active row blocks, rounded up to 1, 2 or 4 of a half (a
+  // wave-uniform choice; every instantiation passes the same barriers).
+  template <bool RPF = false>
+  __device__ __forceinline__ static void run_valid(int rows, GemmSmem<256, 256, 2>& sm,
+                                                   __amdgpu_buffer_rsrc_t ra,
+                                                   const uint32_t (&a_off)[A_BLK],
+                                                   __amdgpu_buffer_rsrc_t rb,
+                                                   const uint32_t (&b_off)[B_BLK], int K, int wv,
+                                                   int lane, acc_t (&acc)[MI][NI],
+                                                   const ResPf& rp = ResPf{}, int kshift = 0) {
+    const int wm = wv >> 2;
+    const int c0 = (rows - wm * 64 + SH - 1) / SH;        // blocks of the first half
+    const int c1 = (rows - 128 - wm * 64 + SH - 1) / SH;  // of the second
+    if (c1 > 2) run_rows<4, 4, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+    else if (c1 > 1) run_rows<4, 2, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+    else if (c1 > 0) run_rows<4, 1, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+    else if (c0 > 2) run_rows<4, 0, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+    else if (c0 > 1) run_rows<2, 0, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+    else if (c0 > 0) run_rows<1, 0, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+    else run_rows<0, 0, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+  }
+
+  // B-tile row -> column of the tile.  Wave wn's columns are the two half
+  // tiles' rows 32 wn .. + 31: 64 consecutive columns (plain outputs, heads of
+  // 64), or the matching 32-column pieces of a 128-wide head's halves, so that
+  // rotary pairs stay in one wave's accumulators: column group g pairs with
+  // group g + 2 either way.
+  __device__ __forceinline__ static int wave_col(int kind, int wn, int head_dim) {
+    const bool split = (kind == EPI_QKV || kind == EPI_QKV_NORM) && head_dim == 128;
+    return split ? (wn >> 1) * 128 + (wn & 1) * 32 : 64 * wn;
+  }
+  __device__ __forceinline__ static int half_step(int kind, int head_dim) {
+    return (kind == EPI_QKV || kind == EPI_QKV_NORM) && head_dim == 128 ? 64 : 32;
+  }
+  __device__ __forceinline__ static int b_row(int kind, int tn, int nt, int ffn, int head_dim) {
+    const int g = nt >> 7, wn = (nt >> 5) & 3, c = nt & 31;
+    if (kind == EPI_SWIGLU) {
+      const int f = tn * 128 + 32 * wn + c;
+      return g ? ffn + f : f;
+    }
+    return tn * 256 + wave_col(kind, wn, head_dim) + g * half_step(kind, head_dim) + c;
   }
 };
 
@@ -372,32 +583,35 @@ struct Mainloop {
 // and column groups >= N are not written (N is a multiple of 4).  Operands
 // of a lane's row (residual) are loaded for a whole row block before any
 // store, at clamped addresses, so no load waits behind a store.
-template <int SH, int MI, int NI, int EK>
+// The second half of a wave's column groups starts hs columns after the first
+// (half the wave's columns, unless the tile deals a head's halves apart).
+template <int SH, int MI, int NI, int EK, int RH = 0>
 __device__ __forceinline__ void plain_epilogue(
     const typename Mfma<SH>::acc_t (&acc)[MI][NI], const Epi& epi, int row0, int row_lim,
-    int col0, int N) {
-  using Geo = AccGeo<SH, MI, NI>;
+    int col0, int N, int hs = NI * SH / 2) {
+  using Geo = AccGeo<SH, MI, NI, RH>;
   constexpr int G = Geo::G;
+  auto gcol = [&](int g) { return g < G / 2 ? Geo::col(g) : Geo::col(g - G / 2) + hs; };
   constexpr int KIND = EK & kEpiKindMask;
   using T = typename Store<(EK & kEpiF32) != 0>::T;
   typedef T T4 __attribute__((ext_vector_type(4)));
   const T* __restrict__ resid = (const T*)epi.resid;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int row = row0 + SH * i;
+    const int row = row0 + Geo::row(i);
     const int rc = min(row, row_lim - 1);
     T4 res[G];
     if constexpr (KIND == EPI_RESID) {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const int col = min(col0 + Geo::col(g), N - 4);
+        const int col = min(col0 + gcol(g), N - 4);
         res[g] = *(const T4*)(resid + (int64_t)rc * epi.ldr + col);
       }
     }
     if (row >= row_lim) continue;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const int col = col0 + Geo::col(g);
+      const int col = col0 + gcol(g);
       if (col >= N) continue;
       const f32x4 v = Geo::grp(acc, i, g);
       if constexpr (KIND == EPI_STORE_F32) {
@@ -420,19 +634,22 @@ __device__ __forceinline__ void plain_epilogue(
 // into LDS (ResPf): tile-relative row tr / column tc of the lane's first group
 // (row0 - tile row0 and col0 - tile col0), kt_par = KT % 2.  The caller has
 // waited for the prefetch loads and passed a barrier.
-template <int SH, int MI, int NI>
+template <int SH, int MI, int NI, int RH>
 __device__ __forceinline__ void resid_lds_epilogue(
     const typename Mfma<SH>::acc_t (&acc)[MI][NI], const Epi& epi, int row0, int row_lim,
     int col0, int N, const char* smem, int kt_par, int tr, int tc) {
-  using Geo = AccGeo<SH, MI, NI>;
+  using Geo = AccGeo<SH, MI, NI, RH>;
   constexpr int G = Geo::G;
-  constexpr int kRegion = 256 * kBK * 2;  // bytes of one buffer's A (or B) region
+  constexpr int kRegion = 128 * kBK * 2;  // bytes of one half tile
   typedef bf16 T4 __attribute__((ext_vector_type(4)));
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int row = row0 + SH * i, r = tr + SH * i;
-    const int h = r >> 7, reg = (r >> 6) & 1, rr = r & 63;
-    const char* rbase = smem + reg * 2 * kRegion + ((kt_par + h) & 1) * kRegion + rr * 512;
+    const int row = row0 + Geo::row(i), r = tr + Geo::row(i);
+    const int h = r >> 7, reg = (r >> 5) & 3, rr = r & 31;
+    // half tile reg of the buffer: A halves 0 and 1, then (past both A
+    // buffers) B halves 0 and 1
+    const char* rbase = smem + (reg >> 1) * 4 * kRegion + ((kt_par + h) & 1) * 2 * kRegion +
+                        (reg & 1) * kRegion + rr * 512;
     T4 res[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -456,16 +673,16 @@ __device__ __forceinline__ void resid_lds_epilogue(
 // SwiGLU: the first half of a wave's columns holds gate rows, the second half
 // the matching up rows (b_row_of), so group g < G / 2 pairs with g + G / 2;
 // f0 = output column (intermediate index) of the lane's first group.
-template <int SH, int MI, int NI, bool F32>
+template <int SH, int MI, int NI, bool F32, int RH = 0>
 __device__ __forceinline__ void swiglu_epilogue(const typename Mfma<SH>::acc_t (&acc)[MI][NI],
                                                 const Epi& epi, int row0, int row_lim, int f0) {
-  using Geo = AccGeo<SH, MI, NI>;
+  using Geo = AccGeo<SH, MI, NI, RH>;
   constexpr int G = Geo::G;
   using T = typename Store<F32>::T;
   typedef T T4 __attribute__((ext_vector_type(4)));
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int row = row0 + SH * i;
+    const int row = row0 + Geo::row(i);
     if (row >= row_lim) continue;
 #pragma unroll
     for (int g = 0; g < G / 2; ++g) {
@@ -484,17 +701,17 @@ __device__ __forceinline__ void swiglu_epilogue(const typename Mfma<SH>::acc_t (
 // one q (KIND 0), k (1) or v (2) head: the lane's token row, head-dim values
 // d + (col(g0 + u) - col(g0)) + e of the first half and the same plus D / 2
 // from group g0 + u + GH.
-template <int KIND, int SH, int MI, int NI, int GH, int QB, bool F32>
+template <int KIND, int SH, int MI, int NI, int GH, int QB, bool F32, int RH = 0>
 __device__ __forceinline__ void qkv_block(const typename Mfma<SH>::acc_t (&acc)[MI][NI],
                                           const Epi& epi, int i, int g0, int D, int row0, int M,
                                           int head, int d, const float (&b1)[QB][4],
                                           const float (&b2)[QB][4]) {
-  using Geo = AccGeo<SH, MI, NI>;
+  using Geo = AccGeo<SH, MI, NI, RH>;
   const int half = D / 2;
   using T = typename Store<F32>::T;
   typedef T T4 __attribute__((ext_vector_type(4)));
   const int Hq = epi.n_q_heads, Hkv = epi.n_kv_heads;
-  const int row = row0 + SH * i;
+  const int row = row0 + Geo::row(i);
   const int rc = min(row, M - 1);
   f32x4 cs[QB][2];  // (cos, sin) of the group's 4 values: [u][0] = e 0..1, [u][1] = e 2..3
   int sl = 0, tr = 0;
@@ -587,6 +804,109 @@ __device__ __forceinline__ void qkv_epilogue(const typename Mfma<SH>::acc_t (&ac
         qkv_block<2, SH, MI, NI, GH, QB, F32>(acc, epi, i, g0, D, row0, M, head, d, b1, b2);
     }
   }
+}
+
+// The q/k/v epilogue of the ping-pong tiles: the wave's column groups 0 and 1
+// are first-half values of one head, groups 2 and 3 their rotary partners
+// (PingLoop::wave_col).  NORM: the per-head RMSNorm of q and k; a lane and
+// the three others of its row hold 64 of the head's values, the other 64 of a
+// 128-wide head are the neighbour wave's (wn ^ 1), whose sums of squares come
+// through LDS (free past the main loop), as do the gains.
+struct QkvNormSmem {
+  float ss[8][128];   // [wave][row of the wave]
+  float gain[2][128];  // q, k
+};
+
+template <int KIND, bool NORM, bool F32>
+__device__ __forceinline__ void qkv_ping_rows(PingLoop::acc_t (&acc)[8][4], const Epi& epi,
+                                              const QkvNormSmem& sm, int wv, int row0, int M,
+                                              int head, int d, const float (&b1)[2][4],
+                                              const float (&b2)[2][4]) {
+  constexpr int SH = 16, MI = 8, NI = 4, RH = PingLoop::RH;
+  constexpr bool NRM = NORM && KIND != 2;
+  const int D = epi.head_dim, lr = threadIdx.x & 15;
+  const float z[2][4] = {};
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if constexpr (NRM) {
+      float ss = sm.ss[wv][16 * i + lr];
+      if (D == 128) ss += sm.ss[wv ^ 1][16 * i + lr];
+      const float r = 1.0f / sqrtf(ss / (float)D + epi.eps);
+      // (the bias is added here, and not again below)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const f32x4 g1 = *(const f32x4*)&sm.gain[KIND][d + 16 * u];
+        const f32x4 g2 = *(const f32x4*)&sm.gain[KIND][d + 16 * u + D / 2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[i][u][e] = (acc[i][u][e] + b1[u][e]) * (r * g1[e]);
+          acc[i][u + 2][e] = (acc[i][u + 2][e] + b2[u][e]) * (r * g2[e]);
+        }
+      }
+      qkv_block<KIND, SH, MI, NI, 2, 2, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, z, z);
+    } else {
+      qkv_block<KIND, SH, MI, NI, 2, 2, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, b1, b2);
+    }
+    if constexpr (NORM) __builtin_amdgcn_sched_barrier(0);  // one row block at a time: no spills
+  }
+}
+
+template <bool NORM, bool F32>
+__device__ __forceinline__ void qkv_ping_epilogue(PingLoop::acc_t (&acc)[8][4], const Epi& epi,
+                                                  char* smem, int wv, int lane, int tile_row,
+                                                  int tile_col, int M, int N) {
+  using St = Store<F32>;
+  constexpr int MI = 8;
+  const int wm = wv >> 2, wn = wv & 3;
+  const int lr = lane & 15, lc = 4 * (lane >> 4);
+  const int D = epi.head_dim, half = D / 2, Hq = epi.n_q_heads, Hkv = epi.n_kv_heads;
+  const int wcol = tile_col + PingLoop::wave_col(EPI_QKV, wn, D);
+  const bool live = wcol < N;  // wave-uniform (whole heads: N is a multiple of D)
+  const int col = (live ? wcol : 0) + lc;
+  const int head = col / D, d = col % D;
+  const int kind = __builtin_amdgcn_readfirstlane(head < Hq ? 0 : (head < Hq + Hkv ? 1 : 2));
+  const int row0 = tile_row + wm * 64 + lr;
+  QkvNormSmem& sm = *reinterpret_cast<QkvNormSmem*>(smem);
+  float b1[2][4], b2[2][4];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      b1[u][e] = epi.bias ? St::ld(epi.bias, col + 16 * u + e) : 0.f;
+      b2[u][e] = epi.bias ? St::ld(epi.bias, col + 16 * u + e + half) : 0.f;
+    }
+  if constexpr (NORM) {
+    __syncthreads();  // every wave is done with the main loop's LDS
+    if (threadIdx.x < 256) {
+      const int w = threadIdx.x >> 7, c = threadIdx.x & 127;
+      if (c < D) sm.gain[w][c] = St::ld(w ? epi.k_norm : epi.q_norm, c);
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      float ss = 0.f;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x1 = acc[i][u][e] + b1[u][e], x2 = acc[i][u + 2][e] + b2[u][e];
+          ss += x1 * x1 + x2 * x2;
+        }
+      ss += __shfl_xor(ss, 16, 64);
+      ss += __shfl_xor(ss, 32, 64);
+      if (lane < 16) sm.ss[wv][16 * i + lr] = ss;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    // (the biased sums are formed again below: kept from here, they would spill)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) asm("" : "+v"(b1[u][e]), "+v"(b2[u][e]));
+  }
+  if (!live) return;
+  if (kind == 0) qkv_ping_rows<0, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
+  else if (kind == 1) qkv_ping_rows<1, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
+  else qkv_ping_rows<2, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
 }
 
 // The q/k/v epilogue with the per-head RMSNorm of q and k.  The sum of
@@ -716,9 +1036,14 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
                                                    int N, int K, int kc, Epi epi,
                                                    int tiles_m, int tiles_n, int full,
                                                    int tsplit, float* __restrict__ tail) {
-  using ML = Mainloop<BM, BN, WGM, WGN, S, SH>;
-  using Geo = AccGeo<SH, ML::MI, ML::NI>;
-  constexpr int NW = ML::NW, WM = ML::WM, WN = ML::WN, MI = ML::MI, NI = ML::NI;
+  // 256 x 256 tiles: the ping-pong loop
+  constexpr bool PP = BM == 256 && BN == 256;
+  static_assert(!PP || (WGM == 2 && WGN == 4 && S == 2 && SH == 16), "ping-pong wave layout");
+  using ML = std::conditional_t<PP, PingLoop, Mainloop<BM, BN, WGM, WGN, S, SH>>;
+  constexpr int RH = PP ? PingLoop::RH : 0;
+  using Geo = AccGeo<SH, ML::MI, ML::NI, RH>;
+  constexpr int NW = ML::NW, MI = ML::MI, NI = ML::NI;
+  constexpr int WM = PP ? 64 : BM / WGM, WN = BN / WGN;
   constexpr int KIND = EK & kEpiKindMask;
   constexpr bool F32 = (EK & kEpiF32) != 0;
   extern __shared__ __align__(16) char smem_raw[];
@@ -775,15 +1100,16 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
 #pragma unroll
   for (int j = 0; j < ML::B_BLK; ++j) {
     const int tr = (wv + NW * j) * 8 + lrow;
-    const int gr = b_row_of<BN, WN>(KIND, tn, tr, epi.ffn);
+    int gr;
+    if constexpr (PP) gr = PingLoop::b_row(KIND, tn, tr, epi.ffn, epi.head_dim);
+    else gr = b_row_of<BN, WN>(KIND, tn, tr, epi.ffn);
     b_off[j] = gr < n_rows_b ? (uint32_t)(((int64_t)gr * ldb + swz(tr, lane & 7) * 8) * 2) : 0x80000000u;
   }
   typename ML::acc_t acc[MI][NI];
   const int lr = Geo::lane_row(lane), lc = Geo::lane_col(lane);
   // bf16 residual epilogue of a whole 256 x 256 tile: prefetch the residual
   // into the LDS buffers freed by the last two k-tiles (ResPf)
-  constexpr bool kResPf = KIND == EPI_RESID && !F32 && BM == 256 && BN == 256 && S == 2 &&
-                          NW == 8;
+  constexpr bool kResPf = KIND == EPI_RESID && !F32 && PP;
   // The descriptor is built unconditionally (only `on` depends on the split):
   // a descriptor assigned under a run-time branch ends up in private memory,
   // and a kernel with a private segment slows every later dispatch on its
@@ -798,34 +1124,45 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
                           (((lane & 31) ^ ((2 * wv + (lane >> 5)) & 15)) << 4)),
                ld_bytes, u < 0 && K / kBK >= 2};
   }
-  ML::template run_valid<MI, kResPf>(M - tm * BM, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane,
-                                     acc, rp);
+  if constexpr (PP)
+    ML::template run_valid<kResPf>(M - tm * BM, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc,
+                                   rp);
+  else
+    ML::run_valid(M - tm * BM, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc);
+  // the wave's first column within the tile, and its second half's distance
+  int wcol = wn * WN, hs = WN / 2;
+  if constexpr (PP) {
+    wcol = PingLoop::wave_col(KIND, wn, epi.head_dim);
+    hs = PingLoop::half_step(KIND, epi.head_dim);
+  }
 
   if (u >= 0) {  // tail split: the tile's fp32 partial sums, [BM][BN]
     Epi e{};
     e.out = tail + (int64_t)u * BM * BN;
     e.ldo = BN;
-    plain_epilogue<SH, MI, NI, EPI_STORE_F32>(acc, e, wm * WM + lr, BM, wn * WN + lc, BN);
+    plain_epilogue<SH, MI, NI, EPI_STORE_F32, RH>(acc, e, wm * WM + lr, BM, wcol + lc, BN, hs);
     return;
   }
   const int row0 = tm * BM + wm * WM + lr;
   if constexpr (KIND == EPI_STORE_F32) {
     Epi e = epi;
     e.out = (float*)epi.out + (int64_t)blockIdx.y * M * epi.ldo;
-    plain_epilogue<SH, MI, NI, EK>(acc, e, row0, M, tn * BN + wn * WN + lc, N);
+    plain_epilogue<SH, MI, NI, EK, RH>(acc, e, row0, M, tn * BN + wn * WN + lc, N);
   } else if constexpr (KIND == EPI_STORE || KIND == EPI_RESID) {
     if constexpr (kResPf) {
       if (rp.on) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // every wave's residual pieces have landed
-        resid_lds_epilogue<SH, MI, NI>(acc, epi, row0, M, tn * BN + wn * WN + lc, N, smem_raw,
+        resid_lds_epilogue<SH, MI, NI, RH>(acc, epi, row0, M, tn * BN + wn * WN + lc, N, smem_raw,
                                        (K / kBK) & 1, wm * WM + lr, wn * WN + lc);
         return;
       }
     }
-    plain_epilogue<SH, MI, NI, EK>(acc, epi, row0, M, tn * BN + wn * WN + lc, N);
+    plain_epilogue<SH, MI, NI, EK, RH>(acc, epi, row0, M, tn * BN + wn * WN + lc, N);
   } else if constexpr (KIND == EPI_SWIGLU) {
-    swiglu_epilogue<SH, MI, NI, F32>(acc, epi, row0, M, tn * (BN / 2) + wn * (WN / 2) + lc);
+    swiglu_epilogue<SH, MI, NI, F32, RH>(acc, epi, row0, M, tn * (BN / 2) + wn * (WN / 2) + lc);
+  } else if constexpr (PP) {
+    qkv_ping_epilogue<KIND == EPI_QKV_NORM, F32>(acc, epi, smem_raw, wv, lane, tm * BM, tn * BN, M,
+                                                 N);
   } else if constexpr (KIND == EPI_QKV_NORM) {
     static_assert(NW * SH * WN * sizeof(float) <= sizeof(GemmSmem<BM, BN>),
                   "the epilogue's row blocks must fit the mainloop's LDS");
@@ -849,9 +1186,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_grouped_kernel(
     const bf16* __restrict__ B, int64_t b_stride, int N, int K,
     const int32_t* __restrict__ seg, const int32_t* __restrict__ tile_off, int n_experts,
     int tiles_n, Epi epi) {
-  using ML = Mainloop<BM, BN, WGM, WGN, 2, SH>;
-  using Geo = AccGeo<SH, ML::MI, ML::NI>;
-  constexpr int NW = ML::NW, WM = ML::WM, WN = ML::WN, MI = ML::MI, NI = ML::NI;
+  constexpr bool PP = BM == 256 && BN == 256;
+  static_assert(!PP || (WGM == 2 && WGN == 4 && SH == 16), "ping-pong wave layout");
+  using ML = std::conditional_t<PP, PingLoop, Mainloop<BM, BN, WGM, WGN, 2, SH>>;
+  constexpr int RH = PP ? PingLoop::RH : 0;
+  using Geo = AccGeo<SH, ML::MI, ML::NI, RH>;
+  constexpr int NW = ML::NW, MI = ML::MI, NI = ML::NI;
+  constexpr int WM = PP ? 64 : BM / WGM, WN = BN / WGN;
   constexpr int KIND = EK & kEpiKindMask;
   constexpr bool F32 = (EK & kEpiF32) != 0;
   extern __shared__ __align__(16) char smem_raw[];
@@ -899,7 +1240,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_grouped_kernel(
 #pragma unroll
   for (int j = 0; j < ML::B_BLK; ++j) {
     const int tr = (wv + NW * j) * 8 + lrow;
-    const int gr = b_row_of<BN, WN>(KIND, tn, tr, epi.ffn);
+    int gr;
+    if constexpr (PP) gr = PingLoop::b_row(KIND, tn, tr, epi.ffn, 0);
+    else gr = b_row_of<BN, WN>(KIND, tn, tr, epi.ffn);
     b_off[j] = gr < n_rows_b ? (uint32_t)(((int64_t)gr * K + swz(tr, lane & 7) * 8) * 2) : 0x80000000u;
   }
   typename ML::acc_t acc[MI][NI];
@@ -916,9 +1259,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_grouped_kernel(
   const int lr = Geo::lane_row(lane), lc = Geo::lane_col(lane);
   const int row0 = p0 + wm * WM + lr;
   if constexpr (KIND == EPI_SWIGLU)
-    swiglu_epilogue<SH, MI, NI, F32>(acc, epi, row0, p_end, tn * (BN / 2) + wn * (WN / 2) + lc);
+    swiglu_epilogue<SH, MI, NI, F32, RH>(acc, epi, row0, p_end,
+                                         tn * (BN / 2) + wn * (WN / 2) + lc);
   else
-    plain_epilogue<SH, MI, NI, EK>(acc, epi, row0, p_end, tn * BN + wn * WN + lc, N);
+    plain_epilogue<SH, MI, NI, EK, RH>(acc, epi, row0, p_end, tn * BN + wn * WN + lc, N);
 }
 
 template <typename Kern>
@@ -1200,14 +1544,14 @@ hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, in
     constexpr int F = kEpiF32;
     switch (epi.kind) {
       case EPI_RESID:
-        return run_gemm_tail<256, 256, 4, 2, EPI_RESID | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-      case EPI_SWIGLU: return run_gemm<256, 256, 4, 2, EPI_SWIGLU | F, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, s);
+        return run_gemm_tail<256, 256, 2, 4, EPI_RESID | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      case EPI_SWIGLU: return run_gemm<256, 256, 2, 4, EPI_SWIGLU | F, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, s);
       case EPI_STORE_F32:
-        return run_gemm_tail<256, 256, 4, 2, EPI_STORE_F32, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+        return run_gemm_tail<256, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
       case EPI_QKV:
         if (epi.q_norm)
-          return run_gemm_tail<256, 256, 4, 2, EPI_QKV_NORM | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-        return run_gemm_tail<256, 256, 4, 2, EPI_QKV | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+          return run_gemm_tail<256, 256, 2, 4, EPI_QKV_NORM | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+        return run_gemm_tail<256, 256, 2, 4, EPI_QKV | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
       default: return hipErrorInvalidValue;
     }
   }
@@ -1245,14 +1589,14 @@ hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, in
   if (epi.kind == EPI_SWIGLU && M <= 640)
     return run_gemm<128, 256, 2, 4, EPI_SWIGLU, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
   switch (epi.kind) {
-    case EPI_STORE: return run_gemm_tail<256, 256, 4, 2, EPI_STORE, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-    case EPI_RESID: return run_gemm_tail<256, 256, 4, 2, EPI_RESID, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-    case EPI_SWIGLU: return run_gemm<256, 256, 4, 2, EPI_SWIGLU, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, s);
-    case EPI_STORE_F32: return run_gemm_tail<256, 256, 4, 2, EPI_STORE_F32, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_STORE: return run_gemm_tail<256, 256, 2, 4, EPI_STORE, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_RESID: return run_gemm_tail<256, 256, 2, 4, EPI_RESID, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_SWIGLU: return run_gemm<256, 256, 2, 4, EPI_SWIGLU, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, s);
+    case EPI_STORE_F32: return run_gemm_tail<256, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
     default:
       if (epi.q_norm)
-        return run_gemm_tail<256, 256, 4, 2, EPI_QKV_NORM, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-      return run_gemm_tail<256, 256, 4, 2, EPI_QKV, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+        return run_gemm_tail<256, 256, 2, 4, EPI_QKV_NORM, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      return run_gemm_tail<256, 256, 2, 4, EPI_QKV, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
   }
 }
 
@@ -1294,7 +1638,7 @@ hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t
       return run_grouped<32, 256, 1, 4, EK>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
                                             tile_off, n_experts, max_tiles_m, epi, s);
     if (bm == 256)
-      return run_grouped<256, 256, 4, 2, EK, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
+      return run_grouped<256, 256, 2, 4, EK, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
                                              tile_off, n_experts, max_tiles_m, epi, s);
     return run_grouped<128, 256, 2, 4, EK, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
                                            tile_off, n_experts, max_tiles_m, epi, s);
@@ -1308,9 +1652,9 @@ hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t
   }
   if (bm == 256) {
     if (epi.kind == EPI_SWIGLU)
-      return run_grouped<256, 256, 4, 2, EPI_SWIGLU, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
+      return run_grouped<256, 256, 2, 4, EPI_SWIGLU, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
                                                       seg, tile_off, n_experts, max_tiles_m, epi, s);
-    return run_grouped<256, 256, 4, 2, EPI_STORE_F32, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N,
+    return run_grouped<256, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N,
                                                        K, seg, tile_off, n_experts, max_tiles_m, epi,
                                                        s);
   }
