@@ -130,6 +130,39 @@ struct AccGeo {
   __device__ __forceinline__ static int lane_col(int lane) { return 4 * (lane / SH); }
 };
 
+// Stores of 16-bit outputs from 16 x 16 accumulator blocks.  A lane holds
+// four consecutive columns of each of the groups g and g + 1 (16 columns
+// apart): stored as they are, every instruction writes 32-byte pieces of 16
+// rows, quarter lines that the memory side takes at ~2.5 TB/s.  One exchange
+// between neighbouring 16-lane rows gives each lane eight consecutive columns
+// of one group, 64-byte pieces per row: lane row lg then holds columns
+// 16 (lg % 2) + 8 (lg / 2) .. + 7 of the 32, i.e. its first column moves by
+// pair_shift().  (Lanes of one token row only ever exchange with each other,
+// so a predicate on the row may be off for both; the exchange is its own
+// inverse.)  A 4096 x 4096 output of one round of tiles: 15.3 -> 12.2 us at
+// K = 64; 16384 x 37888 x 3584 3150 -> 3055 us.
+__device__ __forceinline__ u32x4 pair_swap(u32x4 v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v[0], v[2], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(v[1], v[3], false, false);
+  return u32x4{a[0], b[0], a[1], b[1]};
+}
+__device__ __forceinline__ int pair_shift() { return 12 * ((threadIdx.x >> 4) & 1); }
+__device__ __forceinline__ u32x4 pack_pair(f32x4 v0, f32x4 v1) {
+  return u32x4{pack_bf16x2(v0[0], v0[1]), pack_bf16x2(v0[2], v0[3]), pack_bf16x2(v1[0], v1[1]),
+               pack_bf16x2(v1[2], v1[3])};
+}
+// Eight columns from `col` of a row at p (wide: p + 8 columns 16-byte aligned;
+// otherwise two 8-byte stores), those past N not written.
+__device__ __forceinline__ void store_pair(bf16* p, u32x4 v, int col, int N, bool wide) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  if (wide && col + 8 <= N) {
+    stg16(p, v);
+  } else {
+    if (col < N) *(u32x2*)p = u32x2{v[0], v[1]};
+    if (col + 4 < N) *(u32x2*)(p + 4) = u32x2{v[2], v[3]};
+  }
+}
+
 // MFMA shapes per tile family: the compute-bound prefill tiles (256 x 256,
 // the grouped expert tiles of 128 or 256 rows) and the mid-size-M tiles.  The
 // weight-streaming decode tiles keep 32 x 32 blocks.
@@ -596,6 +629,51 @@ __device__ __forceinline__ void plain_epilogue(
   using T = typename Store<(EK & kEpiF32) != 0>::T;
   typedef T T4 __attribute__((ext_vector_type(4)));
   const T* __restrict__ resid = (const T*)epi.resid;
+  if constexpr (SH == 16 && sizeof(T) == 2 && KIND != EPI_STORE_F32) {
+    static_assert(G % 4 == 0, "pairs of groups within a half");
+    const bool wide = (epi.ldo & 7) == 0 && (KIND != EPI_RESID || (epi.ldr & 7) == 0);
+    const int c0 = col0 + pair_shift();
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int row = row0 + Geo::row(i);
+      const int rc = min(row, row_lim - 1);
+      u32x4 res[G / 2];
+      if constexpr (KIND == EPI_RESID) {
+        // (clamped: groups of four columns, N is a multiple of 4)
+        const T* rp = resid + (int64_t)rc * epi.ldr;
+#pragma unroll
+        for (int q = 0; q < G / 2; ++q) {
+          const int col = c0 + gcol(2 * q);
+          if (wide) {
+            res[q] = ldg16(rp + min(col, N - 8));
+          } else {
+            const u32x2 a = *(const u32x2*)(rp + min(col, N - 4));
+            const u32x2 b = *(const u32x2*)(rp + min(col + 4, N - 4));
+            res[q] = u32x4{a[0], a[1], b[0], b[1]};
+          }
+        }
+      }
+      if (row >= row_lim) continue;
+#pragma unroll
+      for (int q = 0; q < G / 2; ++q) {
+        f32x4 v0 = Geo::grp(acc, i, 2 * q), v1 = Geo::grp(acc, i, 2 * q + 1);
+        if constexpr (KIND == EPI_RESID) {
+          Pack8 r;
+          r.u = pair_swap(res[q]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v0[e] += bf2f(r.e[e]);
+            v1[e] += bf2f(r.e[4 + e]);
+          }
+        }
+        const int col = c0 + gcol(2 * q);
+        store_pair((bf16*)epi.out + (int64_t)row * epi.ldo + col, pair_swap(pack_pair(v0, v1)), col,
+                   N, wide);
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const int row = row0 + Geo::row(i);
@@ -641,6 +719,7 @@ __device__ __forceinline__ void resid_lds_epilogue(
   using Geo = AccGeo<SH, MI, NI, RH>;
   constexpr int G = Geo::G;
   constexpr int kRegion = 128 * kBK * 2;  // bytes of one half tile
+  const bool wide = (epi.ldo & 7) == 0;
   typedef bf16 T4 __attribute__((ext_vector_type(4)));
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
@@ -658,14 +737,16 @@ __device__ __forceinline__ void resid_lds_epilogue(
     }
     if (row >= row_lim) continue;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int col = col0 + Geo::col(g);
-      if (col >= N) continue;
-      const f32x4 v = Geo::grp(acc, i, g);
-      T4 o;
+    for (int q = 0; q < G / 2; ++q) {
+      f32x4 v0 = Geo::grp(acc, i, 2 * q), v1 = Geo::grp(acc, i, 2 * q + 1);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = (bf16)(v[e] + (float)res[g][e]);
-      *(T4*)((bf16*)epi.out + (int64_t)row * epi.ldo + col) = o;
+      for (int e = 0; e < 4; ++e) {
+        v0[e] += (float)res[2 * q][e];
+        v1[e] += (float)res[2 * q + 1][e];
+      }
+      const int col = col0 + pair_shift() + Geo::col(2 * q);
+      store_pair((bf16*)epi.out + (int64_t)row * epi.ldo + col, pair_swap(pack_pair(v0, v1)), col,
+                 N, wide);
     }
   }
 }
@@ -684,6 +765,23 @@ __device__ __forceinline__ void swiglu_epilogue(const typename Mfma<SH>::acc_t (
   for (int i = 0; i < MI; ++i) {
     const int row = row0 + Geo::row(i);
     if (row >= row_lim) continue;
+    if constexpr (SH == 16 && !F32) {
+      // (ffn is a multiple of 64: whole pairs of groups, 16-byte stores)
+#pragma unroll
+      for (int q = 0; q < G / 4; ++q) {
+        f32x4 o[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const f32x4 gt = Geo::grp(acc, i, 2 * q + u), up = Geo::grp(acc, i, 2 * q + u + G / 2);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[u][e] = silu(gt[e]) * up[e];
+        }
+        const int f = f0 + pair_shift() + Geo::col(2 * q);
+        const u32x4 v = pair_swap(pack_pair(o[0], o[1]));
+        if (f < epi.ffn) stg16((bf16*)epi.out + (int64_t)row * epi.ldo + f, v);
+      }
+      continue;
+    }
 #pragma unroll
     for (int g = 0; g < G / 2; ++g) {
       const int f = f0 + Geo::col(g);
@@ -737,11 +835,10 @@ __device__ __forceinline__ void qkv_block(const typename Mfma<SH>::acc_t (&acc)[
     const int kvh = KIND == 1 ? head - Hq : head - Hq - Hkv;
     p = (T*)(KIND == 1 ? epi.kc : epi.vc) + (((int64_t)sl * Hkv + kvh) * epi.max_seq + tr) * D + d;
   }
+  f32x4 o1[QB], o2[QB];
 #pragma unroll
   for (int u = 0; u < QB; ++u) {
-    const int dc = Geo::col(g0 + u) - Geo::col(g0);
     const f32x4 v1 = Geo::grp(acc, i, g0 + u), v2 = Geo::grp(acc, i, g0 + u + GH);
-    T4 o1, o2;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float x1 = v1[e] + b1[u][e], x2 = v2[e] + b2[u][e];
@@ -752,11 +849,31 @@ __device__ __forceinline__ void qkv_block(const typename Mfma<SH>::acc_t (&acc)[
         x1 = y1;
         x2 = y2;
       }
-      o1[e] = (T)x1;
-      o2[e] = (T)x2;
+      o1[u][e] = x1;
+      o2[u][e] = x2;
     }
-    *(T4*)(p + dc) = o1;
-    *(T4*)(p + dc + half) = o2;
+  }
+  if constexpr (SH == 16 && !F32 && QB % 2 == 0) {
+    T* const ps = p + pair_shift();
+#pragma unroll
+    for (int u = 0; u < QB; u += 2) {
+      const int dc = Geo::col(g0 + u) - Geo::col(g0);
+      stg16(ps + dc, pair_swap(pack_pair(o1[u], o1[u + 1])));
+      stg16(ps + dc + half, pair_swap(pack_pair(o2[u], o2[u + 1])));
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < QB; ++u) {
+      const int dc = Geo::col(g0 + u) - Geo::col(g0);
+      T4 s1, s2;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s1[e] = (T)o1[u][e];
+        s2[e] = (T)o2[u][e];
+      }
+      *(T4*)(p + dc) = s1;
+      *(T4*)(p + dc + half) = s2;
+    }
   }
 }
 

@@ -4,7 +4,8 @@ an adjacent value, at most 1% adjacent; see test_gpu_linear.py).
 
 256 x 256 ping-pong tiles: one, two and an odd number of k-tiles; a last M-tile
 of 1, 17, 65, 129, 193 rows (every count of active row blocks, of one wave
-group or both); a last N-tile of 4 columns.
+group or both); a last N-tile of 4 columns (rows not 16-byte aligned: the
+narrow stores).  Mid-size 128-row tiles with such rows too.
 """
 import numpy as np
 import pytest
@@ -24,9 +25,13 @@ PING = [
     (4225, 4096, 320),   # 129 rows
     (4289, 3844, 448),   # 193 rows, 4 columns
 ]
+MID = [
+    (200, 700, 256),     # 128 x 128 tiles, rows of 1400 bytes
+    (1500, 4076, 256),   # 128 x 256 tiles, rows of 8152 bytes
+]
 
 
-@pytest.mark.parametrize("M,N,K", PING)
+@pytest.mark.parametrize("M,N,K", PING + MID)
 def test_gemm_tile_edges(M, N, K):
     import torch
     a_bits, b_bits = normal_bf16(21, 1, (M, K)), normal_bf16(21, 2, (N, K), std=0.05)
