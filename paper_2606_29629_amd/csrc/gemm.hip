@@ -226,7 +226,7 @@ struct Mainloop {
   static constexpr int NT = WGM * WGN * 64;
   static constexpr int NW = NT / 64;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
-  static constexpr int MI = WM / SH, NI = WN / SH;
+  static constexpr int MI = WM / SH, NI = WN / SH, RH = 0;
   static constexpr int A_BLK = BM / 8 / NW, B_BLK = BN / 8 / NW;  // 1 KB blocks per wave
   static constexpr int KSTEPS = kBK / MF::KSTEP;
   static_assert(WM % SH == 0 && WN % SH == 0, "wave tile of whole MFMA blocks");
@@ -384,6 +384,36 @@ struct Mainloop {
   }
 };
 
+// Columns of the ping-pong tiles (HB = 1 or 2: 128 HB columns, four waves
+// across).  A wave's LDS rows of B are 32 wn .. + 31 of every 128-row half
+// tile; b_row says which weight row each holds, so that the wave's column
+// groups of 16 are its 32 HB consecutive output columns or, for SwiGLU and
+// q/k/v, HB groups of one half (gate; first half of a head) and then their
+// HB partners (up; second half): group g pairs with group g + HB in the same
+// lane.
+template <int HB>
+struct PingCols {
+  static constexpr int WC = 32 * HB;   // columns per wave
+  // first column of wave wn, and the distance of its second HB groups
+  __device__ __forceinline__ static int wave_col(int kind, int wn, int head_dim) {
+    const bool qkv = kind == EPI_QKV || kind == EPI_QKV_NORM;
+    const int wph = qkv ? head_dim / WC : 1;  // waves that share a head
+    return (wn / wph) * wph * WC + (wn % wph) * (WC / 2);
+  }
+  __device__ __forceinline__ static int half_step(int kind, int head_dim) {
+    return kind == EPI_QKV || kind == EPI_QKV_NORM ? head_dim / 2 : WC / 2;
+  }
+  __device__ __forceinline__ static int b_row(int kind, int tn, int nt, int ffn, int head_dim) {
+    const int wn = (nt >> 5) & 3, g = HB == 2 ? nt >> 7 : (nt >> 4) & 1;
+    const int c = HB == 2 ? nt & 31 : nt & 15;
+    if (kind == EPI_SWIGLU) {
+      const int f = tn * 64 * HB + wn * 16 * HB + c;
+      return g ? ffn + f : f;
+    }
+    return tn * 128 * HB + wave_col(kind, wn, head_dim) + g * half_step(kind, head_dim) + c;
+  }
+};
+
 // The 256 x 256 tiles' K loop: eight waves in two groups (waves 0-3 and 4-7,
 // one of each group on every SIMD) that run the same program half a phase
 // apart, so that on each SIMD one wave's MFMAs run while the other reads its
@@ -419,7 +449,7 @@ struct Mainloop {
 // Without the stagger of the groups 868 us; loads issued between the MFMAs
 // 840 us; s_setprio, the order of reads and loads in a phase and the order of
 // the MFMAs make no difference.
-struct PingLoop {
+struct PingLoop : PingCols<2> {
   static constexpr int SH = 16, BM = 256, BN = 256, NW = 8, NT = 512;
   using MF = Mfma<SH>;
   using acc_t = MF::acc_t;
@@ -588,27 +618,173 @@ struct PingLoop {
     else run_rows<0, 0, RPF>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
   }
 
-  // B-tile row -> column of the tile.  Wave wn's columns are the two half
-  // tiles' rows 32 wn .. + 31: 64 consecutive columns (plain outputs, heads of
-  // 64), or the matching 32-column pieces of a 128-wide head's halves, so that
-  // rotary pairs stay in one wave's accumulators: column group g pairs with
-  // group g + 2 either way.
-  __device__ __forceinline__ static int wave_col(int kind, int wn, int head_dim) {
-    const bool split = (kind == EPI_QKV || kind == EPI_QKV_NORM) && head_dim == 128;
-    return split ? (wn >> 1) * 128 + (wn & 1) * 32 : 64 * wn;
-  }
-  __device__ __forceinline__ static int half_step(int kind, int head_dim) {
-    return (kind == EPI_QKV || kind == EPI_QKV_NORM) && head_dim == 128 ? 64 : 32;
-  }
-  __device__ __forceinline__ static int b_row(int kind, int tn, int nt, int ffn, int head_dim) {
-    const int g = nt >> 7, wn = (nt >> 5) & 3, c = nt & 31;
-    if (kind == EPI_SWIGLU) {
-      const int f = tn * 128 + 32 * wn + c;
-      return g ? ffn + f : f;
+};
+
+// The same staggered scheme for 128-row tiles of 128 HB columns (HB = 1, 2):
+// a wave owns 64 x 32 HB outputs, HB phases of 16 MFMAs per k-tile.
+//   HB = 2, three stages:  phase 0 reads A, B0 (t), loads B1 (t + 2)
+//                          phase 1 reads B1 (t), loads A, B0 (t + 3)
+//   HB = 1, five stages:   reads A, B (t), loads A, B (t + 4)
+// A phase's reads are waited for before its first barrier, so a stage is
+// loaded again from the next phase on: the four (three) youngest phases'
+// loads, up to 96 KB per CU, stay in flight.
+// What bounds it: one k-tile's loads (32 or 48 KB) take as long from L2 as its
+// MFMAs.  The four- and eight-wave loops with one barrier per k-tile that
+// these replace waited for LDS and for each load burst instead.
+template <int HB>
+struct PingSmall : PingCols<HB> {
+  static constexpr int SH = 16, BM = 128, BN = 128 * HB, NW = 8, NT = 512;
+  static constexpr int S = HB == 1 ? 5 : 3;
+  using MF = Mfma<SH>;
+  using acc_t = MF::acc_t;
+  using Smem = GemmSmem<BM, BN, S>;
+  static constexpr int MI = 4, NI = 2 * HB, RH = 0;
+  static constexpr int A_BLK = 2, B_BLK = 2 * HB;
+  static constexpr int KS = 2;
+
+  template <int C>
+  __device__ __forceinline__ static void run_rows(Smem& sm, __amdgpu_buffer_rsrc_t ra,
+                                                  const uint32_t (&a_off)[A_BLK],
+                                                  __amdgpu_buffer_rsrc_t rb,
+                                                  const uint32_t (&b_off)[B_BLK], int K, int wv,
+                                                  int lane, acc_t (&acc)[MI][NI], int kshift) {
+    const int wm = wv >> 2, wn = wv & 3;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = acc_t{0.f};
+    const int KT = K / kBK;
+    // k-tile kt's A (op 0) or half h of B (op 1): two 1 KB pieces per wave; past
+    // the last k-tile zeros, so that every phase issues the same loads
+    auto gload = [&](int kt, int op, int h) {
+      const int st = kt % S;
+      bf16* dst = (op ? sm.b[st] : sm.a[st]) + h * 128 * kBK + wv * 8 * kBK;
+      const int kk = kt + kshift;
+      const int kb = (kk >= KT ? kk - KT : kk) * kBK * 2;
+      const uint32_t kill = kt < KT ? 0u : 0x80000000u;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        buffer_load_lds16(op ? rb : ra, dst + j * 64 * kBK, (op ? b_off[2 * h + j] : a_off[j]) | kill,
+                          kb);
+    };
+    uint32_t a_base[KS], b_base[KS];
+    {
+      const int lr = lane % SH, lg = lane / SH;
+      const int ra0 = wm * 64 + lr, rb0 = wn * 32 + lr;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int ch = ks * 4 + lg;
+        a_base[ks] = (uint32_t)((ra0 * kBK + swz(ra0, ch) * 8) * 2);
+        b_base[ks] = (uint32_t)((rb0 * kBK + swz(rb0, ch) * 8) * 2);
+      }
     }
-    return tn * 256 + wave_col(kind, wn, head_dim) + g * half_step(kind, head_dim) + c;
+    bf16x8 fa[4][KS], fb[HB][2][KS];
+    auto read_a = [&](int st) {
+      const char* p = (const char*)sm.a[st];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < C; ++i) fa[i][ks] = *(const bf16x8*)(p + a_base[ks] + i * SH * kBK * 2);
+    };
+    auto read_b = [&](int st, auto half) {
+      constexpr int h = decltype(half)::value;
+      const char* p = (const char*)(sm.b[st] + h * 128 * kBK);
+      if constexpr (C > 0) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            fb[h][j][ks] = *(const bf16x8*)(p + b_base[ks] + j * SH * kBK * 2);
+      }
+    };
+    auto barrier = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // 12 loads stay in flight either way: HB = 1, the three youngest k-tiles;
+    // HB = 2, the loads of the four youngest phases
+    auto phase = [&](auto half) {
+      constexpr int h = decltype(half)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
+      barrier();
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][2 * h + j] = MF::mma(fb[h][j][ks], fa[i][ks], acc[i][2 * h + j]);
+      __builtin_amdgcn_s_setprio(0);
+      barrier();
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, HB - 1>;
+    if constexpr (HB == 1) {
+      for (int t = 0; t < S - 1; ++t) {
+        gload(t, 0, 0);
+        gload(t, 1, 0);
+      }
+    } else {
+      gload(0, 0, 0);
+      gload(0, 1, 0);
+      gload(0, 1, 1);
+      gload(1, 0, 0);
+      gload(1, 1, 0);
+      gload(1, 1, 1);
+      gload(2, 0, 0);
+      gload(2, 1, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");  // the first phase's tiles
+    barrier();
+    if (wm) barrier();
+    int st = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      read_a(st);
+      read_b(st, I0{});
+      if constexpr (HB == 1) {
+        gload(kt + S - 1, 0, 0);
+        gload(kt + S - 1, 1, 0);
+        phase(I0{});
+      } else {
+        gload(kt + 2, 1, 1);
+        phase(I0{});
+        read_b(st, I1{});
+        gload(kt + 3, 0, 0);
+        gload(kt + 3, 1, 0);
+        phase(I1{});
+      }
+      st = st + 1 == S ? 0 : st + 1;
+    }
+    if (!wm) barrier();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land after the end
+  }
+  __device__ __forceinline__ static void run_valid(int rows, Smem& sm, __amdgpu_buffer_rsrc_t ra,
+                                                   const uint32_t (&a_off)[A_BLK],
+                                                   __amdgpu_buffer_rsrc_t rb,
+                                                   const uint32_t (&b_off)[B_BLK], int K, int wv,
+                                                   int lane, acc_t (&acc)[MI][NI],
+                                                   const ResPf& = ResPf{}, int kshift = 0) {
+    const int c = (rows - (wv >> 2) * 64 + SH - 1) / SH;
+    if (c > 2) run_rows<4>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
+    else if (c > 1) run_rows<2>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
+    else if (c > 0) run_rows<1>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
+    else run_rows<0>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
   }
 };
+
+// Main loop of a tile form: 2 x 4 waves on 16 x 16 blocks are the ping-pong
+// forms (256 x 256, 128 x 256, 128 x 128).
+template <int BM, int BN, int WGM, int WGN, int S, int SH>
+constexpr bool is_ping() {
+  return WGM == 2 && WGN == 4 && SH == 16;
+}
+template <int BM, int BN, int WGM, int WGN, int S, int SH>
+using MainloopOf = std::conditional_t<
+    is_ping<BM, BN, WGM, WGN, S, SH>(),
+    std::conditional_t<BM == 256, PingLoop, PingSmall<BN / 128>>, Mainloop<BM, BN, WGM, WGN, S, SH>>;
 
 // Epilogues.  The accumulators are read by column group (AccGeo): row0 =
 // output row of the lane in row block 0 (including l % SH); col0 = output
@@ -630,7 +806,8 @@ __device__ __forceinline__ void plain_epilogue(
   typedef T T4 __attribute__((ext_vector_type(4)));
   const T* __restrict__ resid = (const T*)epi.resid;
   if constexpr (SH == 16 && sizeof(T) == 2 && KIND != EPI_STORE_F32) {
-    static_assert(G % 4 == 0, "pairs of groups within a half");
+    // pairs of groups within a half (of two groups, the halves are adjacent)
+    static_assert(G % 4 == 0 || G == 2, "whole pairs");
     const bool wide = (epi.ldo & 7) == 0 && (KIND != EPI_RESID || (epi.ldr & 7) == 0);
     const int c0 = col0 + pair_shift();
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -765,7 +942,7 @@ __device__ __forceinline__ void swiglu_epilogue(const typename Mfma<SH>::acc_t (
   for (int i = 0; i < MI; ++i) {
     const int row = row0 + Geo::row(i);
     if (row >= row_lim) continue;
-    if constexpr (SH == 16 && !F32) {
+    if constexpr (SH == 16 && !F32 && G >= 4) {
       // (ffn is a multiple of 64: whole pairs of groups, 16-byte stores)
 #pragma unroll
       for (int q = 0; q < G / 4; ++q) {
@@ -877,116 +1054,74 @@ __device__ __forceinline__ void qkv_block(const typename Mfma<SH>::acc_t (&acc)[
   }
 }
 
-// q/k/v split + bias + rotary embedding + KV-cache write on the accumulators.
-// HB = D / 64.  A half head is GH = D / 2 / SH * QN groups, so a first-half
-// group g pairs with g + GH (same lane, same element).  The groups are taken
-// QB at a time (QB <= GH, all in one half head): the rotary factors (four
-// (cos, sin) pairs per group, 32 contiguous bytes) and, for k/v heads, the
-// token's cache slot and row are loaded before the stores.
-template <int SH, int MI, int NI, int HB, bool F32>
-__device__ __forceinline__ void qkv_epilogue(const typename Mfma<SH>::acc_t (&acc)[MI][NI],
-                                             const Epi& epi, int row0, int col0, int M, int N) {
-  using St = Store<F32>;
-  using Geo = AccGeo<SH, MI, NI>;
-  constexpr int D = HB * 64, half = D / 2;
-  constexpr int GH = half / SH * Geo::QN;
-  constexpr int QB = GH < 4 ? GH : 4;
-  static_assert(GH % QB == 0 && Geo::G % (2 * GH) == 0, "whole heads per wave");
-  const int Hq = epi.n_q_heads, Hkv = epi.n_kv_heads;
-#pragma unroll
-  for (int g0 = 0; g0 < Geo::G; g0 += QB) {
-    if ((g0 / GH) & 1) continue;
-    const int col = col0 + Geo::col(g0);  // first-half column of the lane's first group
-    if (col >= N) continue;
-    const int head = col / D, d = col % D;
-    float b1[QB][4], b2[QB][4];
-#pragma unroll
-    for (int u = 0; u < QB; ++u) {
-      const int dc = Geo::col(g0 + u) - Geo::col(g0);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        b1[u][e] = epi.bias ? St::ld(epi.bias, col + dc + e) : 0.f;
-        b2[u][e] = epi.bias ? St::ld(epi.bias, col + dc + e + half) : 0.f;
-      }
-    }
-    // the head, hence its kind, is uniform across the wave
-    const int kind = __builtin_amdgcn_readfirstlane(head < Hq ? 0 : (head < Hq + Hkv ? 1 : 2));
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      if (kind == 0)
-        qkv_block<0, SH, MI, NI, GH, QB, F32>(acc, epi, i, g0, D, row0, M, head, d, b1, b2);
-      else if (kind == 1)
-        qkv_block<1, SH, MI, NI, GH, QB, F32>(acc, epi, i, g0, D, row0, M, head, d, b1, b2);
-      else
-        qkv_block<2, SH, MI, NI, GH, QB, F32>(acc, epi, i, g0, D, row0, M, head, d, b1, b2);
-    }
-  }
-}
-
-// The q/k/v epilogue of the ping-pong tiles: the wave's column groups 0 and 1
-// are first-half values of one head, groups 2 and 3 their rotary partners
-// (PingLoop::wave_col).  NORM: the per-head RMSNorm of q and k; a lane and
-// the three others of its row hold 64 of the head's values, the other 64 of a
-// 128-wide head are the neighbour wave's (wn ^ 1), whose sums of squares come
-// through LDS (free past the main loop), as do the gains.
+// The q/k/v epilogue of the ping-pong tiles: the wave's first HB column groups
+// are first-half values of one head, the others their rotary partners
+// (PingCols).  NORM: the per-head RMSNorm of q and k; a lane and the three
+// others of its row hold 32 HB of the head's values, the rest are the
+// neighbour waves', whose sums of squares come through LDS (free past the
+// main loop), as do the gains.
 struct QkvNormSmem {
   float ss[8][128];   // [wave][row of the wave]
   float gain[2][128];  // q, k
 };
 
-template <int KIND, bool NORM, bool F32>
-__device__ __forceinline__ void qkv_ping_rows(PingLoop::acc_t (&acc)[8][4], const Epi& epi,
-                                              const QkvNormSmem& sm, int wv, int row0, int M,
-                                              int head, int d, const float (&b1)[2][4],
-                                              const float (&b2)[2][4]) {
-  constexpr int SH = 16, MI = 8, NI = 4, RH = PingLoop::RH;
+template <class ML, int KIND, bool NORM, bool F32>
+__device__ __forceinline__ void qkv_ping_rows(typename ML::acc_t (&acc)[ML::MI][ML::NI],
+                                              const Epi& epi, const QkvNormSmem& sm, int wv,
+                                              int row0, int M, int head, int d,
+                                              const float (&b1)[ML::NI / 2][4],
+                                              const float (&b2)[ML::NI / 2][4]) {
+  constexpr int SH = 16, MI = ML::MI, NI = ML::NI, HB = NI / 2, RH = ML::RH;
   constexpr bool NRM = NORM && KIND != 2;
   const int D = epi.head_dim, lr = threadIdx.x & 15;
-  const float z[2][4] = {};
+  const int wph = D / ML::WC;  // waves that share a head: 1, 2 or 4
+  const float z[HB][4] = {};
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     if constexpr (NRM) {
-      float ss = sm.ss[wv][16 * i + lr];
-      if (D == 128) ss += sm.ss[wv ^ 1][16 * i + lr];
+      const float(*sp)[128] = &sm.ss[wv / wph * wph];
+      float ss = sp[0][16 * i + lr];
+      if (wph > 1) ss += sp[1][16 * i + lr];
+      if (wph > 2) ss += sp[2][16 * i + lr] + sp[3][16 * i + lr];
       const float r = 1.0f / sqrtf(ss / (float)D + epi.eps);
       // (the bias is added here, and not again below)
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
+      for (int u = 0; u < HB; ++u) {
         const f32x4 g1 = *(const f32x4*)&sm.gain[KIND][d + 16 * u];
         const f32x4 g2 = *(const f32x4*)&sm.gain[KIND][d + 16 * u + D / 2];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           acc[i][u][e] = (acc[i][u][e] + b1[u][e]) * (r * g1[e]);
-          acc[i][u + 2][e] = (acc[i][u + 2][e] + b2[u][e]) * (r * g2[e]);
+          acc[i][u + HB][e] = (acc[i][u + HB][e] + b2[u][e]) * (r * g2[e]);
         }
       }
-      qkv_block<KIND, SH, MI, NI, 2, 2, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, z, z);
+      qkv_block<KIND, SH, MI, NI, HB, HB, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, z, z);
     } else {
-      qkv_block<KIND, SH, MI, NI, 2, 2, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, b1, b2);
+      qkv_block<KIND, SH, MI, NI, HB, HB, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, b1, b2);
     }
     if constexpr (NORM) __builtin_amdgcn_sched_barrier(0);  // one row block at a time: no spills
   }
 }
 
-template <bool NORM, bool F32>
-__device__ __forceinline__ void qkv_ping_epilogue(PingLoop::acc_t (&acc)[8][4], const Epi& epi,
-                                                  char* smem, int wv, int lane, int tile_row,
-                                                  int tile_col, int M, int N) {
+template <class ML, bool NORM, bool F32>
+__device__ __forceinline__ void qkv_ping_epilogue(typename ML::acc_t (&acc)[ML::MI][ML::NI],
+                                                  const Epi& epi, char* smem, int wv, int lane,
+                                                  int tile_row, int tile_col, int M, int N) {
   using St = Store<F32>;
-  constexpr int MI = 8;
+  constexpr int MI = ML::MI, HB = ML::NI / 2;
   const int wm = wv >> 2, wn = wv & 3;
   const int lr = lane & 15, lc = 4 * (lane >> 4);
   const int D = epi.head_dim, half = D / 2, Hq = epi.n_q_heads, Hkv = epi.n_kv_heads;
-  const int wcol = tile_col + PingLoop::wave_col(EPI_QKV, wn, D);
+  const int wcol = tile_col + ML::wave_col(EPI_QKV, wn, D);
   const bool live = wcol < N;  // wave-uniform (whole heads: N is a multiple of D)
   const int col = (live ? wcol : 0) + lc;
   const int head = col / D, d = col % D;
   const int kind = __builtin_amdgcn_readfirstlane(head < Hq ? 0 : (head < Hq + Hkv ? 1 : 2));
   const int row0 = tile_row + wm * 64 + lr;
   QkvNormSmem& sm = *reinterpret_cast<QkvNormSmem*>(smem);
-  float b1[2][4], b2[2][4];
+  float b1[HB][4], b2[HB][4];
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int u = 0; u < HB; ++u)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       b1[u][e] = epi.bias ? St::ld(epi.bias, col + 16 * u + e) : 0.f;
@@ -1002,10 +1137,10 @@ __device__ __forceinline__ void qkv_ping_epilogue(PingLoop::acc_t (&acc)[8][4], 
     for (int i = 0; i < MI; ++i) {
       float ss = 0.f;
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < HB; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x1 = acc[i][u][e] + b1[u][e], x2 = acc[i][u + 2][e] + b2[u][e];
+          const float x1 = acc[i][u][e] + b1[u][e], x2 = acc[i][u + HB][e] + b2[u][e];
           ss += x1 * x1 + x2 * x2;
         }
       ss += __shfl_xor(ss, 16, 64);
@@ -1016,135 +1151,14 @@ __device__ __forceinline__ void qkv_ping_epilogue(PingLoop::acc_t (&acc)[8][4], 
     __syncthreads();
     // (the biased sums are formed again below: kept from here, they would spill)
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < HB; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) asm("" : "+v"(b1[u][e]), "+v"(b2[u][e]));
   }
   if (!live) return;
-  if (kind == 0) qkv_ping_rows<0, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
-  else if (kind == 1) qkv_ping_rows<1, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
-  else qkv_ping_rows<2, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
-}
-
-// The q/k/v epilogue with the per-head RMSNorm of q and k.  The sum of
-// squares over a head needs every value of a (token, head) before any can be
-// stored, more registers than the accumulator tile leaves free, so this
-// epilogue goes through LDS (free once every wave is past the mainloop and
-// its last loads have landed): one row block (SH rows) of the wave's tile at
-// a time, each wave in its own SH x WC fp32 region, 16-byte chunks stored at
-// chunk c ^ row (conflict-free column writes and row reads).  Then each lane takes
-// four consecutive rotary pairs of a row: 16 lanes cover a row's WC / 2 = 64
-// pairs, a pass covers 4 rows, and a head's pairs are an aligned group of
-// D / 8 lanes, its sum of squares a group sum.  The lane's columns, bias and
-// gains stay fixed across rows.
-template <int SH, int MI, int NI, bool F32>
-__device__ __forceinline__ void qkv_norm_epilogue(const typename Mfma<SH>::acc_t (&acc)[MI][NI],
-                                                  const Epi& epi, char* smem, int wv, int lane,
-                                                  int wrow0, int wcol0, int M, int N) {
-  using St = Store<F32>;
-  using T = typename St::T;
-  using Geo = AccGeo<SH, MI, NI>;
-  typedef T T4 __attribute__((ext_vector_type(4)));
-  constexpr int WC = NI * SH;
-  static_assert(WC == 128, "16 lanes per row of the wave's columns");
-  const int lr = Geo::lane_row(lane), lg = lane / SH;
-  const int D = epi.head_dim, half = D / 2;
-  const int Hq = epi.n_q_heads, Hkv = epi.n_kv_heads;
-  const int rl = lane >> 4;                       // row within a 4-row pass
-  const int p0 = 4 * (lane & 15);                 // first of the lane's 4 pairs
-  const int hw = p0 / half, d = p0 % half;        // head within the wave's columns
-  const int c1 = hw * D + d, c2 = c1 + half;      // wave columns of the 4 first / second values
-  const bool col_ok = wcol0 + c1 < N;             // whole heads: N is a multiple of D
-  const int col = col_ok ? wcol0 + c1 : 0;
-  const int head = col / D;
-  const int kind = head < Hq ? 0 : (head < Hq + Hkv ? 1 : 2);
-  float b1[4], b2[4], g1[4], g2[4];
-  {
-    const void* bp = epi.bias;
-    const void* gp = kind == 0 ? epi.q_norm : epi.k_norm;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      b1[e] = bp ? St::ld(bp, col + e) : 0.f;
-      b2[e] = bp ? St::ld(bp, col + half + e) : 0.f;
-      g1[e] = kind == 2 ? 1.f : St::ld(gp, d + e);
-      g2[e] = kind == 2 ? 1.f : St::ld(gp, d + half + e);
-    }
-  }
-  const int kvh = kind == 1 ? head - Hq : head - Hq - Hkv;
-  T* const cache = (T*)(kind == 1 ? epi.kc : epi.vc);
-  const float inv_d = 1.0f / (float)D;
-
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  float* __restrict__ buf = (float*)smem + wv * SH * WC;
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    // group g of the row block is row lr, columns col(g) + 4 lg .. + 3
-#pragma unroll
-    for (int g = 0; g < Geo::G; ++g)
-      *(f32x4*)&buf[lr * WC + (((Geo::col(g) / 4 + lg) ^ lr) << 2)] = Geo::grp(acc, i, g);
-    const int rbase = wrow0 + SH * i;
-    // two passes (8 rows) at a time: the rotary factors, cache slots and rows
-    // are loaded before the first store (a store could alias a later load)
-    for (int t0 = 0; t0 < SH; t0 += 8) {
-      if (rbase + t0 >= M) break;  // uniform
-      f32x4 cs[2][2];              // (cos, sin) of pairs d .. d + 3: [pass][0] = 0..1, [1] = 2..3
-      int sl[2], tr[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int rc = min(rbase + t0 + 4 * u + rl, M - 1);
-        const float2* rp = epi.rope + (int64_t)rc * half + d;
-        cs[u][0] = *(const f32x4*)rp;
-        cs[u][1] = *(const f32x4*)(rp + 2);
-        sl[u] = epi.tok_slot[rc];
-        tr[u] = epi.tok_row[rc];
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int t = t0 + 4 * u + rl, row = rbase + t;
-        const f32x4 v1 = *(const f32x4*)&buf[t * WC + (((c1 >> 2) ^ t) << 2)];
-        const f32x4 v2 = *(const f32x4*)&buf[t * WC + (((c2 >> 2) ^ t) << 2)];
-        float x1[4], x2[4], ss = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x1[e] = v1[e] + b1[e];
-          x2[e] = v2[e] + b2[e];
-          ss += x1[e] * x1[e] + x2[e] * x2[e];
-        }
-        // sum over the head's D / 8 lanes (8 or 16, aligned)
-        ss += __shfl_xor(ss, 1, 64);
-        ss += __shfl_xor(ss, 2, 64);
-        ss += __shfl_xor(ss, 4, 64);
-        if (half == 64) ss += __shfl_xor(ss, 8, 64);
-        T4 o1, o2;
-        const float r = 1.0f / sqrtf(ss * inv_d + epi.eps);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float y1 = x1[e], y2 = x2[e];
-          if (kind != 2) {
-            y1 *= r * g1[e];
-            y2 *= r * g2[e];
-            const float c = cs[u][e >> 1][2 * (e & 1)], sn = cs[u][e >> 1][2 * (e & 1) + 1];
-            const float z1 = y1 * c - y2 * sn;
-            const float z2 = y2 * c + y1 * sn;
-            y1 = z1;
-            y2 = z2;
-          }
-          o1[e] = (T)y1;
-          o2[e] = (T)y2;
-        }
-        T* dst = nullptr;
-        if (kind == 0)
-          dst = (T*)epi.q + ((int64_t)row * Hq + head) * D + d;
-        else if (sl[u] >= 0)
-          dst = cache + (((int64_t)sl[u] * Hkv + kvh) * epi.max_seq + tr[u]) * D + d;
-        if (row < M && col_ok && dst) {
-          *(T4*)dst = o1;
-          *(T4*)(dst + half) = o2;
-        }
-      }
-    }
-  }
+  if (kind == 0) qkv_ping_rows<ML, 0, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
+  else if (kind == 1) qkv_ping_rows<ML, 1, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
+  else qkv_ping_rows<ML, 2, NORM, F32>(acc, epi, sm, wv, row0, M, head, d, b1, b2);
 }
 
 template <int BM, int BN, int WGM, int WGN, int EK, int S = 2, int SH = 32>
@@ -1153,11 +1167,9 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
                                                    int N, int K, int kc, Epi epi,
                                                    int tiles_m, int tiles_n, int full,
                                                    int tsplit, float* __restrict__ tail) {
-  // 256 x 256 tiles: the ping-pong loop
-  constexpr bool PP = BM == 256 && BN == 256;
-  static_assert(!PP || (WGM == 2 && WGN == 4 && S == 2 && SH == 16), "ping-pong wave layout");
-  using ML = std::conditional_t<PP, PingLoop, Mainloop<BM, BN, WGM, WGN, S, SH>>;
-  constexpr int RH = PP ? PingLoop::RH : 0;
+  using ML = MainloopOf<BM, BN, WGM, WGN, S, SH>;
+  constexpr bool PP = is_ping<BM, BN, WGM, WGN, S, SH>();
+  constexpr int RH = ML::RH;
   using Geo = AccGeo<SH, ML::MI, ML::NI, RH>;
   constexpr int NW = ML::NW, MI = ML::MI, NI = ML::NI;
   constexpr int WM = PP ? 64 : BM / WGM, WN = BN / WGN;
@@ -1218,7 +1230,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
   for (int j = 0; j < ML::B_BLK; ++j) {
     const int tr = (wv + NW * j) * 8 + lrow;
     int gr;
-    if constexpr (PP) gr = PingLoop::b_row(KIND, tn, tr, epi.ffn, epi.head_dim);
+    if constexpr (PP) gr = ML::b_row(KIND, tn, tr, epi.ffn, epi.head_dim);
     else gr = b_row_of<BN, WN>(KIND, tn, tr, epi.ffn);
     b_off[j] = gr < n_rows_b ? (uint32_t)(((int64_t)gr * ldb + swz(tr, lane & 7) * 8) * 2) : 0x80000000u;
   }
@@ -1226,7 +1238,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
   const int lr = Geo::lane_row(lane), lc = Geo::lane_col(lane);
   // bf16 residual epilogue of a whole 256 x 256 tile: prefetch the residual
   // into the LDS buffers freed by the last two k-tiles (ResPf)
-  constexpr bool kResPf = KIND == EPI_RESID && !F32 && PP;
+  constexpr bool kResPf = KIND == EPI_RESID && !F32 && PP && BM == 256;
   // The descriptor is built unconditionally (only `on` depends on the split):
   // a descriptor assigned under a run-time branch ends up in private memory,
   // and a kernel with a private segment slows every later dispatch on its
@@ -1241,7 +1253,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
                           (((lane & 31) ^ ((2 * wv + (lane >> 5)) & 15)) << 4)),
                ld_bytes, u < 0 && K / kBK >= 2};
   }
-  if constexpr (PP)
+  if constexpr (PP && BM == 256)
     ML::template run_valid<kResPf>(M - tm * BM, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc,
                                    rp);
   else
@@ -1249,15 +1261,17 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
   // the wave's first column within the tile, and its second half's distance
   int wcol = wn * WN, hs = WN / 2;
   if constexpr (PP) {
-    wcol = PingLoop::wave_col(KIND, wn, epi.head_dim);
-    hs = PingLoop::half_step(KIND, epi.head_dim);
+    wcol = ML::wave_col(KIND, wn, epi.head_dim);
+    hs = ML::half_step(KIND, epi.head_dim);
   }
 
   if (u >= 0) {  // tail split: the tile's fp32 partial sums, [BM][BN]
     Epi e{};
     e.out = tail + (int64_t)u * BM * BN;
     e.ldo = BN;
-    plain_epilogue<SH, MI, NI, EPI_STORE_F32, RH>(acc, e, wm * WM + lr, BM, wcol + lc, BN, hs);
+    // (the tile's valid rows only: tail_epi_kernel reads no others)
+    plain_epilogue<SH, MI, NI, EPI_STORE_F32, RH>(acc, e, wm * WM + lr, min(BM, M - tm * BM),
+                                                  wcol + lc, BN, hs);
     return;
   }
   const int row0 = tm * BM + wm * WM + lr;
@@ -1277,19 +1291,17 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
     plain_epilogue<SH, MI, NI, EK, RH>(acc, epi, row0, M, tn * BN + wn * WN + lc, N);
   } else if constexpr (KIND == EPI_SWIGLU) {
     swiglu_epilogue<SH, MI, NI, F32, RH>(acc, epi, row0, M, tn * (BN / 2) + wn * (WN / 2) + lc);
-  } else if constexpr (PP) {
-    qkv_ping_epilogue<KIND == EPI_QKV_NORM, F32>(acc, epi, smem_raw, wv, lane, tm * BM, tn * BN, M,
-                                                 N);
-  } else if constexpr (KIND == EPI_QKV_NORM) {
-    static_assert(NW * SH * WN * sizeof(float) <= sizeof(GemmSmem<BM, BN>),
-                  "the epilogue's row blocks must fit the mainloop's LDS");
-    qkv_norm_epilogue<SH, MI, NI, F32>(acc, epi, smem_raw, wv, lane, tm * BM + wm * WM,
-                                       tn * BN + wn * WN, M, N);
-  } else if (epi.head_dim == 128) {
-    qkv_epilogue<SH, MI, NI, 2, F32>(acc, epi, row0, tn * BN + wn * WN + lc, M, N);
   } else {
-    qkv_epilogue<SH, MI, NI, 1, F32>(acc, epi, row0, tn * BN + wn * WN + lc, M, N);
+    static_assert(PP, "the q/k/v epilogue pairs column groups as PingCols deals them");
+    qkv_ping_epilogue<ML, KIND == EPI_QKV_NORM, F32>(acc, epi, smem_raw, wv, lane, tm * BM, tn * BN, M,
+                                                 N);
   }
+}
+
+// LDS stages of a grouped tile form.
+template <int BM, int BN, int WGM, int WGN, int SH>
+constexpr int grouped_stages() {
+  return is_ping<BM, BN, WGM, WGN, 2, SH>() && BM == 128 ? 3 : 2;
 }
 
 // Grouped expert GEMM.  Rows [seg[e], seg[e+1]) of the routed order belong to
@@ -1303,17 +1315,17 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_grouped_kernel(
     const bf16* __restrict__ B, int64_t b_stride, int N, int K,
     const int32_t* __restrict__ seg, const int32_t* __restrict__ tile_off, int n_experts,
     int tiles_n, Epi epi) {
-  constexpr bool PP = BM == 256 && BN == 256;
-  static_assert(!PP || (WGM == 2 && WGN == 4 && SH == 16), "ping-pong wave layout");
-  using ML = std::conditional_t<PP, PingLoop, Mainloop<BM, BN, WGM, WGN, 2, SH>>;
-  constexpr int RH = PP ? PingLoop::RH : 0;
+  constexpr int S = grouped_stages<BM, BN, WGM, WGN, SH>();
+  using ML = MainloopOf<BM, BN, WGM, WGN, S, SH>;
+  constexpr bool PP = is_ping<BM, BN, WGM, WGN, S, SH>();
+  constexpr int RH = ML::RH;
   using Geo = AccGeo<SH, ML::MI, ML::NI, RH>;
   constexpr int NW = ML::NW, MI = ML::MI, NI = ML::NI;
   constexpr int WM = PP ? 64 : BM / WGM, WN = BN / WGN;
   constexpr int KIND = EK & kEpiKindMask;
   constexpr bool F32 = (EK & kEpiF32) != 0;
   extern __shared__ __align__(16) char smem_raw[];
-  GemmSmem<BM, BN>& sm = *reinterpret_cast<GemmSmem<BM, BN>*>(smem_raw);
+  GemmSmem<BM, BN, S>& sm = *reinterpret_cast<GemmSmem<BM, BN, S>*>(smem_raw);
 
   // The real tiles (tile_off[E] M-tiles x tiles_n) are dealt to the XCDs in
   // contiguous shares (block b runs on XCD b % 8), so an expert's M-tiles run
@@ -1358,7 +1370,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_grouped_kernel(
   for (int j = 0; j < ML::B_BLK; ++j) {
     const int tr = (wv + NW * j) * 8 + lrow;
     int gr;
-    if constexpr (PP) gr = PingLoop::b_row(KIND, tn, tr, epi.ffn, 0);
+    if constexpr (PP) gr = ML::b_row(KIND, tn, tr, epi.ffn, 0);
     else gr = b_row_of<BN, WN>(KIND, tn, tr, epi.ffn);
     b_off[j] = gr < n_rows_b ? (uint32_t)(((int64_t)gr * K + swz(tr, lane & 7) * 8) * 2) : 0x80000000u;
   }
@@ -1435,6 +1447,56 @@ static int tail_tiles(int total) {
 
 constexpr int kMaxTailSplit = 8;  // K-parts of a tail tile, at most
 
+// How a bf16 GEMM of M x N x K runs: on 256 x 256 tiles, the last partial
+// round of them whole (split 1), in `split` K-parts, or as 128-row halves
+// (split 0), or on 128 x 256 or 128 x 128 tiles throughout.  The choice is
+// the least of the forms' estimated times: rounds of workgroups (one per CU)
+// of KT k-tiles, plus per round the fill and the epilogue, plus for a K-split
+// the partials written and read back and one more launch.  The constants are
+// measured at clocks the small GEMMs hold (per k-tile: 256 x 256 1.05 us, 128 x
+// 256 0.74 us, 128 x 128 0.55 us; they are bound by LDS, 256, 176 and 128 KB a
+// k-tile through 128 B per clock, so the largest tile does the most per CU
+// and the small ones only pay where they fill more of the CUs).
+struct GemmPlan {
+  int bm, bn, split;
+};
+constexpr float kUs256 = 1.05f, kUs128x256 = 0.74f, kUs128 = 0.55f;  // us per k-tile
+constexpr float kUsRound256 = 12.f, kUsRound128x256 = 8.f, kUsRound128 = 6.f;  // us per round
+constexpr float kUsLaunch = 5.f;         // one more launch
+constexpr float kPartialMbPerUs = 4.2f;  // fp32 partials, written or read
+
+static GemmPlan gemm_plan(int M, int N, int K, int kind, bool have_tail) {
+  const int G = cu_count(), kt = K / kBK;
+  const int cols256 = cdiv(N, 256), t256 = cdiv(M, 256) * cols256;
+  const bool swiglu = kind == EPI_SWIGLU;
+  GemmPlan best{256, 256, 1};
+  float cost = cdiv(t256, G) * (kt * kUs256 + kUsRound256);
+  auto offer = [&](float c, GemmPlan p) {
+    if (c < cost) {
+      cost = c;
+      best = p;
+    }
+  };
+  const int rem = tail_tiles(t256);
+  const float rounds = (t256 - rem) / G * (kt * kUs256 + kUsRound256);
+  if (rem > 0) {
+    offer(rounds + cdiv(2 * rem, G) * (kt * kUs128x256 + kUsRound128x256) +
+              (t256 > rem ? kUsLaunch : 0.f),
+          {256, 256, 0});
+    if (have_tail && !swiglu)
+      for (int t = 2; t <= kMaxTailSplit && t * rem <= G && (t - 1) * cdiv(kt, t) < kt; ++t)
+        offer(rounds + cdiv(kt, t) * kUs256 + kUsRound256 + 2 * kUsLaunch +
+                  2 * rem * t * 0.262f / kPartialMbPerUs,
+              {256, 256, t});
+  }
+  offer(cdiv(cdiv(M, 128) * cols256, G) * (kt * kUs128x256 + kUsRound128x256), {128, 256, 1});
+  if (!swiglu)
+    offer(cdiv(cdiv(M, 128) * cdiv(N, 128), G) * (kt * kUs128 + kUsRound128), {128, 128, 1});
+  return best;
+}
+
+// The K-split of the fp32 storage mode's tail tiles (and of fp32 outputs): as
+// many parts as fill the round.
 static int tail_split(int total, int K, int kind) {
   const int G = cu_count();
   const int rem = tail_tiles(total);
@@ -1474,12 +1536,17 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
   tile_of_id(full + j, tiles_m, tiles_n, tm, tn);
   const float* __restrict__ tp = tail + (int64_t)j * tsplit * BM * BN;
   const int e0 = blockIdx.x * kTailChunk + threadIdx.x;
+  // rows past M hold no partials: a workgroup of such rows has nothing to do,
+  // and loads of a partly valid one stay within the valid rows
+  constexpr int kRow = QKV ? BN / 2 : BN;  // elements per tile row
+  if (tm * BM + (int)blockIdx.x * kTailChunk / kRow >= M) return;
+  const int e_end = min(BM, M - tm * BM) * kRow;
   if constexpr (!QKV) {
     int idx[kTailPer];
     float v[kTailPer];
 #pragma unroll
     for (int q = 0; q < kTailPer; ++q) {
-      idx[q] = min(e0 + 256 * q, BM * BN - 1);
+      idx[q] = min(e0 + 256 * q, e_end - 1);
       v[q] = 0.f;
     }
     // every plane's values are loaded before the ordered sum (tsplit <=
@@ -1507,7 +1574,7 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
     for (int q = 0; q < kTailPer; ++q) {
       const int e = e0 + 256 * q;
       const int row = tm * BM + e / BN, col = tn * BN + e % BN;
-      if (e >= BM * BN || row >= M || col >= N) continue;
+      if (e >= e_end || col >= N) continue;
       if (epi.kind == EPI_STORE_F32) {
         ((float*)epi.out)[(int64_t)row * epi.ldo + col] = v[q];
       } else {
@@ -1525,7 +1592,7 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
     float x1[kTailPer], x2[kTailPer];
 #pragma unroll
     for (int q = 0; q < kTailPer; ++q) {
-      const int e = min(e0 + 256 * q, BM * (BN / 2) - 1);
+      const int e = min(e0 + 256 * q, e_end - 1);
       const int pc = e % (BN / 2);
       rr[q] = e / (BN / 2);
       cc[q] = (pc / half) * Dh + pc % half;  // first-half column in the tile
@@ -1573,7 +1640,7 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
 #pragma unroll
     for (int q = 0; q < kTailPer; ++q) {
       const int row = tm * BM + rr[q], col = tn * BN + cc[q];
-      if (e0 + 256 * q >= BM * (BN / 2) || row >= M || col >= N) continue;
+      if (e0 + 256 * q >= e_end || col >= N) continue;
       const int head = col / Dh, d = col % Dh;
       float y1 = x1[q], y2 = x2[q];
       if (head < Hq + Hkv) {
@@ -1601,12 +1668,11 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
 
 template <int BM, int BN, int WGM, int WGN, int EK, int SH = 32>
 static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, int M, int N,
-                                int K, const Epi& epi, float* tail, hipStream_t s) {
+                                int K, const Epi& epi, float* tail, hipStream_t s, int t) {
   constexpr int KIND = EK & kEpiKindMask;
   const int tiles_m = cdiv(M, BM);
   const int tiles_n = KIND == EPI_SWIGLU ? cdiv(epi.ffn, BN / 2) : cdiv(N, BN);
   const int total = tiles_m * tiles_n;
-  const int t = tail ? tail_split(total, K, KIND) : 1;
   if (t == 1) return run_gemm<BM, BN, WGM, WGN, EK, 2, SH>(A, lda, B, ldb, M, N, K, epi, s);
   const int n_tail = tail_tiles(total);
   const int full = total - n_tail;
@@ -1614,15 +1680,10 @@ static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, 
   static bool attr_set = false;
   hipError_t e = opt_in_lds(gemm_kernel<BM, BN, WGM, WGN, EK, 2, SH>, smem, attr_set);
   if (e != hipSuccess) return e;
-  // A tail split in two or three (a final round a quarter to a half full), or
-  // in four over a short K, of a bf16-output 256 x 256 GEMM runs instead as
-  // 128-row halves of the tail tiles over the whole K: the same round of work
-  // (or a little more) with no fp32 partials and no reduction kernel.
-  constexpr bool kHalfOk = BM == 256 && BN == 256 && !(EK & kEpiF32) &&
-                           (KIND == EPI_STORE || KIND == EPI_RESID || KIND == EPI_QKV ||
-                            KIND == EPI_QKV_NORM);
-  if constexpr (kHalfOk) {
-    if (t <= 3 || (t == 4 && K <= 4096)) {
+  // t = 0: the tail tiles run as a second launch of their 128-row halves over
+  // the whole K, with no fp32 partials and no reduction kernel.
+  if constexpr (BM == 256 && BN == 256 && !(EK & kEpiF32) && KIND != EPI_STORE_F32) {
+    if (t == 0) {
       if (full > 0) {
         gemm_kernel<BM, BN, WGM, WGN, EK, 2, SH><<<full, WGM * WGN * 64, smem, s>>>(
             (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, K, epi, tiles_m, tiles_n, full, 1,
@@ -1630,18 +1691,17 @@ static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, 
         e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
-      // q/k/v keep 128 columns per wave (rotary pairs); the others 64 x 64 waves
-      constexpr int HM = (KIND == EPI_QKV || KIND == EPI_QKV_NORM) ? 4 : 2;
       const size_t hsmem = sizeof(GemmSmem<128, 256, 3>);
       static bool half_attr = false;
-      e = opt_in_lds(gemm_kernel<128, 256, HM, 8 / HM, EK, 3, kMidSH>, hsmem, half_attr);
+      e = opt_in_lds(gemm_kernel<128, 256, 2, 4, EK, 3, kMidSH>, hsmem, half_attr);
       if (e != hipSuccess) return e;
-      gemm_kernel<128, 256, HM, 8 / HM, EK, 3, kMidSH><<<2 * n_tail, 512, hsmem, s>>>(
+      gemm_kernel<128, 256, 2, 4, EK, 3, kMidSH><<<2 * n_tail, 512, hsmem, s>>>(
           (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, K, epi, tiles_m, tiles_n, full, 0,
           nullptr);
       return hipGetLastError();
     }
   }
+  if (KIND == EPI_SWIGLU) return hipErrorInvalidValue;  // (its tail is never split in K)
   gemm_kernel<BM, BN, WGM, WGN, EK, 2, SH><<<full + n_tail * t, WGM * WGN * 64, smem, s>>>(
       (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, K, epi, tiles_m, tiles_n, full, t, tail);
   e = hipGetLastError();
@@ -1654,66 +1714,55 @@ static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, 
   return hipGetLastError();
 }
 
+template <int EK>
+static hipError_t run_planned(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
+                              const Epi& epi, float* tail, hipStream_t s) {
+  constexpr int KIND = EK & kEpiKindMask;
+  const GemmPlan p = gemm_plan(M, KIND == EPI_SWIGLU ? 2 * epi.ffn : N, K, KIND, tail != nullptr);
+  if (p.bm == 256)
+    return run_gemm_tail<256, 256, 2, 4, EK, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s,
+                                                         p.split);
+  if constexpr (KIND != EPI_SWIGLU) {
+    if (p.bn == 128)
+      return run_gemm<128, 128, 2, 4, EK, 5, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
+  }
+  return run_gemm<128, 256, 2, 4, EK, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
+}
+
+// fp32 storage and fp32 outputs: 256 x 256 tiles, the tail split in K.
+template <int EK>
+static hipError_t run_tail_split(const void* A, int lda, const void* B, int ldb, int M, int N,
+                                 int K, const Epi& epi, float* tail, hipStream_t s) {
+  constexpr int KIND = EK & kEpiKindMask;
+  const int n = KIND == EPI_SWIGLU ? cdiv(epi.ffn, 128) : cdiv(N, 256);
+  const int t = tail ? tail_split(cdiv(M, 256) * n, K, KIND) : 1;
+  return run_gemm_tail<256, 256, 2, 4, EK, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s, t);
+}
+
 hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                        const Epi& epi, float* tail, hipStream_t s) {
   if (M == 0) return hipSuccess;
+  if (epi.kind == EPI_STORE_F32)
+    return run_tail_split<EPI_STORE_F32>(A, lda, B, ldb, M, N, K, epi, tail, s);
   if (epi.f32) {
     constexpr int F = kEpiF32;
     switch (epi.kind) {
-      case EPI_RESID:
-        return run_gemm_tail<256, 256, 2, 4, EPI_RESID | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-      case EPI_SWIGLU: return run_gemm<256, 256, 2, 4, EPI_SWIGLU | F, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, s);
-      case EPI_STORE_F32:
-        return run_gemm_tail<256, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      case EPI_RESID: return run_tail_split<EPI_RESID | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      case EPI_SWIGLU: return run_tail_split<EPI_SWIGLU | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
       case EPI_QKV:
         if (epi.q_norm)
-          return run_gemm_tail<256, 256, 2, 4, EPI_QKV_NORM | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-        return run_gemm_tail<256, 256, 2, 4, EPI_QKV | F, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+          return run_tail_split<EPI_QKV_NORM | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
+        return run_tail_split<EPI_QKV | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
       default: return hipErrorInvalidValue;
     }
   }
-  // Mid-size M (a chunk of a few hundred tokens, the mixed step): when the
-  // 256 x 256 tiles would not fill one round of CUs, 128 x 128 tiles of four
-  // 32 x 128 waves with three LDS stages (two k-tiles in flight): a short
-  // k-tile of a small tile computes in less time than a load's round trip,
-  // so two stages leave such a GEMM bound by load latency.  The waves keep
-  // 128 columns (the q/k/v epilogue pairs rotary halves inside a wave).
-  // gate/up at M <= 640: 128 x 256 tiles with three stages (its 256-row
-  // tiles leave most of a third tile empty).  A long K (the down
-  // projection) keeps the 256 x 256 tail split.
-  if (epi.kind != EPI_SWIGLU && epi.kind != EPI_STORE_F32 && K <= 8192 &&
-      cdiv(M, 256) * cdiv(N, 256) < cu_count()) {
-    // Plain and residual stores (no rotary pairs) take 128 x 256 tiles of
-    // eight 64 x 64 waves when those fill one round of CUs at least three
-    // quarters full: a 4096-token O projection is one round of 256 such tiles
-    // instead of two rounds of 128 x 128.
-    const int t256 = cdiv(M, 128) * cdiv(N, 256);
-    if ((epi.kind == EPI_STORE || epi.kind == EPI_RESID) && t256 <= cu_count() &&
-        4 * t256 >= 3 * cu_count()) {
-      if (epi.kind == EPI_STORE)
-        return run_gemm<128, 256, 2, 4, EPI_STORE, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-      return run_gemm<128, 256, 2, 4, EPI_RESID, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-    }
-    switch (epi.kind) {
-      case EPI_STORE: return run_gemm<128, 128, 4, 1, EPI_STORE, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-      case EPI_RESID: return run_gemm<128, 128, 4, 1, EPI_RESID, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-      default:
-        if (epi.q_norm)
-          return run_gemm<128, 128, 4, 1, EPI_QKV_NORM, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-        return run_gemm<128, 128, 4, 1, EPI_QKV, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-    }
-  }
-  if (epi.kind == EPI_SWIGLU && M <= 640)
-    return run_gemm<128, 256, 2, 4, EPI_SWIGLU, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
   switch (epi.kind) {
-    case EPI_STORE: return run_gemm_tail<256, 256, 2, 4, EPI_STORE, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-    case EPI_RESID: return run_gemm_tail<256, 256, 2, 4, EPI_RESID, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-    case EPI_SWIGLU: return run_gemm<256, 256, 2, 4, EPI_SWIGLU, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, s);
-    case EPI_STORE_F32: return run_gemm_tail<256, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_STORE: return run_planned<EPI_STORE>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_RESID: return run_planned<EPI_RESID>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_SWIGLU: return run_planned<EPI_SWIGLU>(A, lda, B, ldb, M, N, K, epi, tail, s);
     default:
-      if (epi.q_norm)
-        return run_gemm_tail<256, 256, 2, 4, EPI_QKV_NORM, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
-      return run_gemm_tail<256, 256, 2, 4, EPI_QKV, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      if (epi.q_norm) return run_planned<EPI_QKV_NORM>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      return run_planned<EPI_QKV>(A, lda, B, ldb, M, N, K, epi, tail, s);
   }
 }
 
@@ -1732,7 +1781,7 @@ static hipError_t run_grouped(const void* A, int lda, int a_rows, const int32_t*
                               const int32_t* tile_off, int n_experts, int max_tiles_m,
                               const Epi& epi, hipStream_t s) {
   const int tiles_n = (EK & kEpiKindMask) == EPI_SWIGLU ? cdiv(epi.ffn, BN / 2) : cdiv(N, BN);
-  const size_t smem = sizeof(GemmSmem<BM, BN>);
+  const size_t smem = sizeof(GemmSmem<BM, BN, grouped_stages<BM, BN, WGM, WGN, SH>()>);
   static bool attr_set = false;
   hipError_t e = opt_in_lds(gemm_grouped_kernel<BM, BN, WGM, WGN, EK, SH>, smem, attr_set);
   if (e != hipSuccess) return e;

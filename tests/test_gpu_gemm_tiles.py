@@ -26,6 +26,9 @@ PING = [
     (4289, 3844, 448),   # 193 rows, 4 columns
 ]
 MID = [
+    (1061, 768, 9472),   # 256 x 256 tiles split in K, 37 valid rows in the last (partials of those only)
+    (900, 1280, 2048),   # 128 x 128 tiles, 4 valid rows in the last
+    (1400, 4352, 512),   # 128 x 256 tiles
     (200, 700, 256),     # 128 x 128 tiles, rows of 1400 bytes
     (1500, 4076, 256),   # 128 x 256 tiles, rows of 8152 bytes
 ]
