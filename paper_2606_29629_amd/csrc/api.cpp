@@ -641,7 +641,13 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
   e.ldo = H;
   e.resid = x_in;
   e.ldr = H;
-  if (skinny_resid_norm_fused(T, H, Hq * D)) {
+  // A few rows: gate/up normalises x1 itself (no norm launch at all).
+  const bool norm_in_gate_up =
+      !moe && stream_norm_ok(T, H) && skinny_resid_norm_fused(T, H, Hq * D);
+  if (norm_in_gate_up) {
+    StageTimer t_(ST_OPROJ, s, timed);
+    if ((st = run_linear(attn, Hq * D, w->w_o, T, H, Hq * D, e, part, s)) != TRI_OK) return st;
+  } else if (skinny_resid_norm_fused(T, H, Hq * D)) {
     // short batch: the O projection's split-K reduction also adds the
     // residual and applies the pre-MLP RMSNorm (no separate norm launch)
     StageTimer t_(ST_OPROJ, s, timed);
@@ -664,7 +670,12 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
     e.ffn = F;
     {
       StageTimer t_(ST_GATEUP, s, timed);
-      if ((st = run_linear(h2, H, w->w_gate_up, T, 2 * F, H, e, part, s)) != TRI_OK) return st;
+      if (norm_in_gate_up)
+        TRI_HIP(launch_stream_norm_swiglu(
+            x1, H, w->w_gate_up, H, T, H, e,
+            StreamNorm{(const __bf16*)w->mlp_norm, (__bf16*)h2, cfg->rms_eps}, s));
+      else if ((st = run_linear(h2, H, w->w_gate_up, T, 2 * F, H, e, part, s)) != TRI_OK)
+        return st;
     }
     e = Epi{};
     e.kind = EPI_RESID;

@@ -81,6 +81,14 @@ __device__ __forceinline__ float silu(float z) {
 __host__ __device__ constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 
+// ---- operand tiles in LDS (GEMMs): rows of 64 bf16.
+// LDS has 64 banks of 4 bytes (a 256-byte window).  A tile row is 128 bytes,
+// so rows r and r+1 share a window; a ds_read_b128 phase of 16 lanes reads the
+// same logical chunk of 16 consecutive rows.  XOR-ing the chunk with
+// (row / 2) % 8 gives the 8 even and the 8 odd rows 8 distinct 16-byte slots
+// each, i.e. all 16 slots of the window: no bank conflict.
+__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+
 // ---- K/V tiles in LDS (attention).  Tile rows are one key's D values
 // (D * 2 bytes); physical 16-byte chunk of logical chunk c in row r:
 //  D = 128 (256-byte rows): c ^ g(r), g(r) = 4 (r % 4) + (r / 4) % 4.  g is a

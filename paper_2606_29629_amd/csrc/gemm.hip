@@ -45,13 +45,6 @@ constexpr int kXcds = 8;
 // Epi still says EPI_QKV; its q_norm pointer selects this instantiation).
 constexpr int EPI_QKV_NORM = 5;
 
-// LDS has 64 banks of 4 bytes (a 256-byte window).  A tile row is 128 bytes,
-// so rows r and r+1 share a window; a ds_read_b128 phase of 16 lanes reads the
-// same logical chunk of 16 consecutive rows.  XOR-ing the chunk with
-// (row / 2) % 8 gives the 8 even and the 8 odd rows 8 distinct 16-byte slots
-// each, i.e. all 16 slots of the window: no bank conflict.
-__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
-
 // XCD-contiguous remap of block id bid among n: the blocks of XCD x (those
 // with bid % 8 == x; dispatch is round-robin over the XCDs) take one
 // contiguous range of ids.
@@ -1996,7 +1989,8 @@ __global__ __launch_bounds__(kNormRowThreads) void splitk_resid_norm_kernel(
   }
 }
 
-// Decode projections (M <= 128 rows).  The arithmetic intensity is ~M flop
+// Decode projections (17 .. 128 rows; fewer run as weight streams,
+// launch_stream).  The arithmetic intensity is ~M flop
 // per weight byte, so the weight stream from HBM sets the time: skinny
 // 64 x 64 tiles (two or four waves) give ~600 workgroups on the large
 // projections -- every one resident at once, each a short run of weight rows,
@@ -2071,9 +2065,27 @@ static hipError_t run_skinny(const void* A, int lda, const void* B, int ldb, int
   return hipGetLastError();
 }
 
+static hipError_t run_stream_plane(const void* A, int lda, const void* B, int ldb, int M, int N,
+                                   int K, float* plane, hipStream_t s) {
+  Epi pe{};
+  pe.kind = EPI_STORE_F32;
+  pe.out = plane;
+  pe.ldo = N;
+  return launch_stream(A, lda, B, ldb, M, N, K, pe, s);
+}
+
 hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                          const Epi& epi, float* part, hipStream_t s) {
   if (M == 0) return hipSuccess;
+  if (M <= kStreamMaxRows) {
+    if (!(epi.kind == EPI_QKV && epi.q_norm)) return launch_stream(A, lda, B, ldb, M, N, K, epi, s);
+    // the q/k norm needs whole heads: one fp32 plane, finished row by row
+    hipError_t e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
+    if (e != hipSuccess) return e;
+    const int64_t n = (int64_t)M * (epi.n_q_heads + 2 * epi.n_kv_heads) * (epi.head_dim / 2);
+    splitk_epi_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(part, 1, M, N, epi);
+    return hipGetLastError();
+  }
   const int splits = skinny_splits(M, N, K, epi.kind);
   if (splits == 1 && epi.kind == EPI_QKV) return launch_gemm(A, lda, B, ldb, M, N, K, epi, nullptr, s);
   if (M <= 64) return run_skinny<64, 2>(A, lda, B, ldb, M, N, K, epi, part, splits, s);
@@ -2089,8 +2101,14 @@ hipError_t launch_skinny_resid_norm(const void* A, int lda, const void* B, int l
                                     int K, const void* resid, int ldr, void* out, int ldo,
                                     const void* g, void* y, float eps, float* part, hipStream_t s) {
   if (M == 0) return hipSuccess;
-  const int splits = skinny_splits(M, N, K, EPI_RESID);
-  hipError_t e = run_skinny_planes(A, lda, B, ldb, M, N, K, part, splits, EPI_RESID, s);
+  int splits = 1;
+  hipError_t e;
+  if (M <= kStreamMaxRows) {
+    e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
+  } else {
+    splits = skinny_splits(M, N, K, EPI_RESID);
+    e = run_skinny_planes(A, lda, B, ldb, M, N, K, part, splits, EPI_RESID, s);
+  }
   if (e != hipSuccess) return e;
   splitk_resid_norm_kernel<<<M, kNormRowThreads, 0, s>>>(part, splits, M, N, (const bf16*)resid,
                                                         ldr, (bf16*)out, ldo, (const bf16*)g,

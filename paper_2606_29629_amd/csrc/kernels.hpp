@@ -132,6 +132,23 @@ size_t skinny_partial_bytes(int M, int N, int K, int kind);
 hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                          const Epi& epi, float* part, hipStream_t s);
 
+// Projections of at most kStreamMaxRows rows as weight streams, the epilogue
+// fused (EPI_QKV without the q/k norm).
+constexpr int kStreamMaxRows = 16;
+hipError_t launch_stream(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
+                         const Epi& epi, hipStream_t s);
+// gate/up (EPI_SWIGLU) on RMSNorm(x), which is written to nrm.h: for the few
+// rows stream_norm_ok allows (they fit in LDS).
+constexpr int kStreamNormMaxElems = 16384, kStreamNormMaxCols = 4096;
+struct StreamNorm {
+  const __bf16* g;  // gains [K]
+  __bf16* h;        // normalised rows [M, K]
+  float eps;
+};
+bool stream_norm_ok(int M, int K);
+hipError_t launch_stream_norm_swiglu(const void* x, int ldx, const void* B, int ldb, int M, int K,
+                                     const Epi& epi, const StreamNorm& nrm, hipStream_t s);
+
 // Causal flash attention for sequences with q_len > 1 (or all when
 // include_single != 0).  A batch with few query tiles but long key ranges
 // splits each query tile's keys over attn_prefill_splits() workgroups, whose
