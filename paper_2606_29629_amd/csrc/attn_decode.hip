@@ -380,8 +380,13 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(
   }
 }
 
-// One workgroup of D threads per (sequence, query head).
-template <int D>
+// One workgroup of D threads per (sequence, query head).  Splits in groups of
+// GS: the group's (m, l, acc) loads are issued together, then folded in split
+// order into a running (M, L, o).  GS = 8 serves the few splits of a full
+// batch; a small batch over long contexts has up to 64, where each group of
+// eight cost a memory round trip (40 splits, one sequence: 8.6 us), so it takes
+// them 32 at a time.
+template <int D, int GS>
 __global__ __launch_bounds__(128) void attn_combine_kernel(
     const float* __restrict__ part, bf16* __restrict__ O, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ ctx_len, const int32_t* __restrict__ slot, int n_slots,
@@ -392,21 +397,19 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(
   if (sl < 0 || sl >= n_slots || c < 0 || c + 1 > max_seq) return;
   const int ns = min(cdiv(c + 1, split_keys), nsplit);  // never past the launched splits
   const float* pp = part + ((int64_t)s * Hq + qh) * nsplit * (D + 2);
-  // Splits in groups of 8: the group's (m, l, acc) loads are issued together,
-  // then folded in split order into a running (M, L, o).
   float M = -INFINITY, Lsum = 0.f, o = 0.f;
-  for (int i0 = 0; i0 < ns; i0 += 8) {
-    float m[8], l[8], a[8];
+  for (int i0 = 0; i0 < ns; i0 += GS) {
+    float m[GS], l[GS], a[GS];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const bool ok = i0 + j < ns;
-      const float* q = pp + (ok ? i0 + j : 0) * (D + 2);
-      m[j] = ok ? q[D] : -INFINITY;
-      l[j] = ok ? q[D + 1] : 0.f;
-      a[j] = ok ? q[d] : 0.f;
+    for (int j = 0; j < GS; ++j) {
+      // (past the last split: the last one again, dropped)
+      const float* q = pp + min(i0 + j, ns - 1) * (D + 2);
+      m[j] = q[D];
+      l[j] = q[D + 1];
+      a[j] = q[d];
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < GS; ++j) {
       if (i0 + j >= ns) break;
       const float Mn = fmaxf(M, m[j]);
       const float sc = exp2f(M - Mn), w = exp2f(m[j] - Mn);
@@ -457,14 +460,13 @@ hipError_t launch_attn_decode_combine(const float* part, void* out, const BatchD
                                            n_q_heads / n_kv_heads, attn_decode_max_split(kv));
   const int nsplit = cdiv(max_kv, split);
   dim3 cgrid(b.n_seqs, n_q_heads);
-  if (head_dim == 128)
-    attn_combine_kernel<128><<<cgrid, 128, 0, s>>>(part, (bf16*)out, b.cu_q, b.ctx_len, b.slot,
-                                                   n_slots, max_seq, n_q_heads, nsplit, split,
-                                                   b.n_tokens);
-  else
-    attn_combine_kernel<64><<<cgrid, 64, 0, s>>>(part, (bf16*)out, b.cu_q, b.ctx_len, b.slot,
-                                                 n_slots, max_seq, n_q_heads, nsplit, split,
-                                                 b.n_tokens);
+  auto run = [&](auto kernel) {
+    kernel<<<cgrid, head_dim, 0, s>>>(part, (bf16*)out, b.cu_q, b.ctx_len, b.slot, n_slots, max_seq,
+                                      n_q_heads, nsplit, split, b.n_tokens);
+  };
+  const bool many = nsplit > 8;
+  if (head_dim == 128) run(many ? attn_combine_kernel<128, 32> : attn_combine_kernel<128, 8>);
+  else run(many ? attn_combine_kernel<64, 32> : attn_combine_kernel<64, 8>);
   return hipGetLastError();
 }
 
