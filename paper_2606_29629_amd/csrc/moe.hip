@@ -25,6 +25,28 @@ constexpr int kRouteChunk = 1024;  // hidden columns staged per pass
 template <typename InT>
 __device__ __forceinline__ float to_f32(InT v) { return (float)v; }
 
+// Maximum over the wave, in every lane, by register moves alone: rotations
+// within 16 lanes, then exchanges of 16- and 32-lane rows.  (A shuffle goes
+// through LDS, ~100 clocks a step: k = 8 selections by twelve shuffles each
+// took 4 us of the top-k kernel's 8.5.)
+__device__ __forceinline__ float wave_max_dpp(float v) {
+#define TRI_ROR_MAX(n)                                                                    \
+  v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                     \
+                                             0, __builtin_bit_cast(int, v), 0x120 + (n),  \
+                                             0xf, 0xf, false)))
+  TRI_ROR_MAX(8);
+  TRI_ROR_MAX(4);
+  TRI_ROR_MAX(2);
+  TRI_ROR_MAX(1);
+#undef TRI_ROR_MAX
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const unsigned w = __builtin_bit_cast(unsigned, v);
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // Top-k of one token's logits (lane holds experts lane + 64 q, q < 4; -inf
 // past E) with ties to the lower expert index, then the softmax weights of the
 // chosen experts (over all experts, or renormalised over the k chosen).
@@ -38,21 +60,16 @@ __device__ __forceinline__ void route_topk(const float (&vin)[4], int E, int k, 
   float my_v = -INFINITY;
   int my_i = 0;
   for (int s = 0; s < k; ++s) {
-    // this lane's best (highest value, then lowest expert index)
-    float bv = v[0];
-    int bi = lane;
+    // the wave's highest logit, then the lowest expert holding it (experts of a
+    // smaller q come first, then those of a lower lane)
+    const float bv = wave_max_dpp(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    int bi = -1;
 #pragma unroll
-    for (int q = 1; q < 4; ++q) {
-      const int e = lane + 64 * q;
-      if (v[q] > bv) { bv = v[q]; bi = e; }
+    for (int q = 0; q < 4; ++q) {
+      const unsigned long long eq = __builtin_amdgcn_ballot_w64(v[q] == bv && lane + 64 * q < E);
+      if (bi < 0 && eq) bi = 64 * q + __builtin_ctzll(eq);
     }
-    if (bv == -INFINITY) bi = 0x7fffffff;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
+    if (bi < 0) bi = min(s, E - 1);  // (no comparable logit: NaNs; any expert of the layer)
     if (lane == s) { my_v = bv; my_i = bi; }
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -297,10 +314,78 @@ __global__ __launch_bounds__(256) void moe_scatter_kernel(
   }
 }
 
+// The whole permutation of a short pair list (a decode step) in one workgroup,
+// one pair per thread: lanes of one expert find each other with a ballot per
+// bit of the expert number, the waves' counts per expert are scanned in LDS,
+// then counts and tile counts over the experts.  Count and scatter as two
+// launches cost 8-9 us of a step whatever the list's length.
+constexpr int kSmallPairs = 1024;
+
+__global__ __launch_bounds__(kSmallPairs) void moe_permute_small_kernel(
+    const int32_t* __restrict__ idx, int n_pairs, int E, int bm, int32_t* __restrict__ perm,
+    int32_t* __restrict__ inv, int32_t* __restrict__ seg, int32_t* __restrict__ tile_off) {
+  constexpr int NW = kSmallPairs / 64;
+  __shared__ int cnt[NW][256];  // pairs of the wave routed to the expert, then those before it
+  __shared__ int off[257], toff[257];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int e = tid < n_pairs ? idx[tid] : -1;
+  for (int i = tid; i < NW * 256; i += kSmallPairs) (&cnt[0][0])[i] = 0;
+  unsigned long long same = __builtin_amdgcn_ballot_w64(tid < n_pairs);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const unsigned long long m = __builtin_amdgcn_ballot_w64((e >> b) & 1);
+    same &= ((e >> b) & 1) ? m : ~m;
+  }
+  const int within = __popcll(same & ((1ull << lane) - 1ull));
+  __syncthreads();
+  if (tid < n_pairs && within == 0) cnt[wave][e] = __popcll(same);
+  __syncthreads();
+  if (tid < 256) {
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int c = cnt[w][tid];
+      cnt[w][tid] = total;
+      total += c;
+    }
+    off[tid + 1] = total;
+    toff[tid + 1] = cdiv(total, bm);
+    if (tid == 0) off[0] = toff[0] = 0;
+  }
+  __syncthreads();
+  for (int d = 1; d < 256; d <<= 1) {  // inclusive scans over the experts
+    int a = 0, b = 0;
+    if (tid < 256 && tid + 1 - d >= 1) {
+      a = off[tid + 1 - d];
+      b = toff[tid + 1 - d];
+    }
+    __syncthreads();
+    if (tid < 256) {
+      off[tid + 1] += a;
+      toff[tid + 1] += b;
+    }
+    __syncthreads();
+  }
+  if (tid <= E) {
+    seg[tid] = off[tid];
+    tile_off[tid] = toff[tid];
+  }
+  if (tid < n_pairs) {
+    const int pos = off[e] + cnt[wave][e] + within;
+    perm[pos] = tid;
+    inv[tid] = pos;
+  }
+}
+
 hipError_t launch_moe_permute(const int32_t* idx, int n_pairs, int E, int bm, int32_t* rank,
                               int32_t* counts, int32_t* perm, int32_t* inv, int32_t* seg,
                               int32_t* tile_off, hipStream_t s) {
   if (n_pairs == 0) return hipSuccess;
+  if (n_pairs <= kSmallPairs) {
+    moe_permute_small_kernel<<<1, kSmallPairs, 0, s>>>(idx, n_pairs, E, bm, perm, inv, seg,
+                                                       tile_off);
+    return hipGetLastError();
+  }
   if (n_pairs > 256 * kCountUnroll)
     moe_count_kernel<16><<<E, 1024, 0, s>>>(idx, n_pairs, rank, counts);
   else

@@ -1,0 +1,43 @@
+"""The routed order of a step (workspace `perm`): pairs grouped by expert,
+ascending within one, at the limits of the one-workgroup permutation (1024
+pairs) and of the expert count, and top-k routes against the reference order
+of the library's own logits (ties to the lower expert: duplicated router rows).
+"""
+import numpy as np
+import pytest
+
+from paper_2606_29629_amd import _lib as T
+from paper_2606_29629_amd.workload import DeviceLayer, device_batch, device_cache, to_device_bf16
+from synth import LayerConfig, make_cache, make_weights, make_x
+from test_gpu_layer import B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("E,k,n", [(3, 1, 5), (1, 1, 64), (256, 16, 64), (128, 8, 128), (128, 8, 129),
+                                   (65, 4, 1)])
+def test_permutation_groups_pairs_by_expert(E, k, n):
+    import torch
+    cfg = LayerConfig(hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=64, n_experts=E, top_k=k,
+                      expert_ffn_dim=64)
+    wb = make_weights(cfg, 51)
+    if E > 64:
+        wb["w_router"][E - 1] = wb["w_router"][0]  # a tie in every token
+    kb, vb = make_cache(cfg, n, 64, 51)
+    dl = DeviceLayer(cfg, wb)
+    db = device_batch(B(list(range(n)), [i % 50 for i in range(n)], [1] * n))
+    idx = torch.empty(n, k, dtype=torch.int32, device="cuda")
+    w = torch.empty(n, k, dtype=torch.float32, device="cuda")
+    _, ws = T.layer_decode(dl.cfg, dl.w, device_cache(kb, vb), db,
+                           to_device_bf16(make_x(cfg, n, 51)), route_idx=idx, route_w=w)
+    torch.cuda.synchronize()
+    m = T.workspace_layout(dl.cfg, db)
+    perm = ws[m.perm:m.perm + 4 * n * k].view(torch.int32).cpu().numpy()
+    idx, w = idx.cpu().numpy(), w.cpu().numpy()
+    assert np.array_equal(perm, np.argsort(idx.ravel(), kind="stable"))
+    assert idx.min() >= 0 and idx.max() < E
+    assert all(len(set(row)) == k for row in idx.tolist())
+    assert np.all(np.diff(w, axis=1) <= 0) and np.allclose(w.sum(1), 1, atol=1e-5)
+    if E > 64:  # the duplicated expert: never ahead of its lower twin
+        for row in idx.tolist():
+            assert E - 1 not in row or (0 in row and row.index(0) < row.index(E - 1))
