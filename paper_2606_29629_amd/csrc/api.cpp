@@ -377,13 +377,18 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   float* act = at<float>(ws, L.act);
   float* tail = at<float>(ws, L.part);
   void* a3 = at<void>(ws, L.a3);
-  auto planes = [&](const void* src, int64_t rows, int cols, int pattern, void* dst) {
-    return launch_split3((const float*)src, cols, rows, cols, pattern, dst, s);
+  void* wqkv3 = at<void>(ws, L.w_qkv3);
+  void* wo3 = at<void>(ws, L.w_o3);
+  void* wgu3 = at<void>(ws, L.w_gu3);
+  void* wd3 = at<void>(ws, L.w_d3);
+  // operand planes of activations whose producer does not write them itself
+  auto planes = [&](const void* src, int64_t rows, int cols, void* dst) {
+    return launch_split3(Split3Jobs{1, {{(const float*)src, rows, cols, 0, dst}}}, s);
   };
   {
     StageTimer t_(ST_PROLOGUE, s, timed);
     TRI_HIP(launch_prologue(bd, kv, D, cfg->rope_base, rope_sections(cfg), tok_slot, tok_row,
-                            rope, x_in, w->attn_norm, h, H, cfg->rms_eps, s, true));
+                            rope, x_in, w->attn_norm, h, H, cfg->rms_eps, s, true, a3));
   }
   Epi e{};
   e.f32 = 1;
@@ -404,13 +409,20 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   e.max_seq = kv.panel_rows();
   {
     StageTimer t_(ST_QKV, s, timed);
-    TRI_HIP(planes(h, T, H, 0, a3));
-    TRI_HIP(planes(w->w_qkv, Nqkv, H, 1, at<void>(ws, L.w_qkv3)));
-    TRI_HIP(launch_gemm(a3, 3 * H, at<void>(ws, L.w_qkv3), 3 * H, T, Nqkv, 3 * H, e, tail, s));
+    // every weight's planes in one launch
+    const int64_t experts = moe ? cfg->n_experts : 1;
+    const int Fw = moe ? cfg->expert_ffn_dim : F;
+    const Split3Jobs jobs{4,
+                          {{(const float*)w->w_qkv, Nqkv, H, 1, wqkv3},
+                           {(const float*)w->w_o, H, Hq * D, 1, wo3},
+                           {(const float*)w->w_gate_up, experts * 2 * Fw, H, 1, wgu3},
+                           {(const float*)w->w_down, experts * H, Fw, 1, wd3}}};
+    TRI_HIP(launch_split3(jobs, s));
+    TRI_HIP(launch_gemm(a3, 3 * H, wqkv3, 3 * H, T, Nqkv, 3 * H, e, tail, s));
   }
   {
     StageTimer t_(ST_ATTN_PREFILL, s, timed);
-    TRI_HIP(launch_attn_prefill(q, cache->k, cache->v, attn, bd, kv, Hq, Hkv, D, 1, nullptr, s,
+    TRI_HIP(launch_attn_prefill(q, cache->k, cache->v, attn, bd, kv, Hq, Hkv, D, 1, (float*)a3, s,
                                 true));
   }
   e = Epi{};
@@ -422,17 +434,12 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   e.ldr = H;
   {
     StageTimer t_(ST_OPROJ, s, timed);
-    TRI_HIP(planes(attn, T, Hq * D, 0, a3));
-    TRI_HIP(planes(w->w_o, H, Hq * D, 1, at<void>(ws, L.w_o3)));
-    TRI_HIP(launch_gemm(a3, 3 * Hq * D, at<void>(ws, L.w_o3), 3 * Hq * D, T, H, 3 * Hq * D, e,
-                        tail, s));
+    TRI_HIP(launch_gemm(a3, 3 * Hq * D, wo3, 3 * Hq * D, T, H, 3 * Hq * D, e, tail, s));
   }
   {
     StageTimer t_(ST_NORM2, s, timed);
-    TRI_HIP(launch_rmsnorm(x1, w->mlp_norm, h2, nullptr, T, H, cfg->rms_eps, s, true));
+    TRI_HIP(launch_rmsnorm(x1, w->mlp_norm, h2, nullptr, T, H, cfg->rms_eps, s, true, a3));
   }
-  void* wgu3 = at<void>(ws, L.w_gu3);
-  void* wd3 = at<void>(ws, L.w_d3);
   if (!moe) {
     e = Epi{};
     e.f32 = 1;
@@ -442,8 +449,6 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
     e.ffn = F;
     {
       StageTimer t_(ST_GATEUP, s, timed);
-      TRI_HIP(planes(h2, T, H, 0, a3));
-      TRI_HIP(planes(w->w_gate_up, 2 * F, H, 1, wgu3));
       TRI_HIP(launch_gemm(a3, 3 * H, wgu3, 3 * H, T, 2 * F, 3 * H, e, tail, s));
     }
     e = Epi{};
@@ -454,8 +459,7 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
     e.resid = x1;
     e.ldr = H;
     StageTimer t_(ST_DOWN, s, timed);
-    TRI_HIP(planes(act, T, F, 0, a3));
-    TRI_HIP(planes(w->w_down, H, F, 1, wd3));
+    TRI_HIP(planes(act, T, F, a3));
     TRI_HIP(launch_gemm(a3, 3 * F, wd3, 3 * F, T, H, 3 * F, e, tail, s));
     return TRI_OK;
   }
@@ -486,8 +490,6 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   e.ffn = Fe;
   {
     StageTimer t_(ST_MOE_GATEUP, s, timed);
-    TRI_HIP(planes(h2, T, H, 0, a3));
-    TRI_HIP(planes(w->w_gate_up, (int64_t)E * 2 * Fe, H, 1, wgu3));
     TRI_HIP(launch_gemm_grouped(a3, 3 * H, T, perm, k, wgu3, (int64_t)2 * Fe * 3 * H, 2 * Fe,
                                 3 * H, seg, tile_off, E, P, e, s));
   }
@@ -498,8 +500,7 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   e.ldo = H;
   {
     StageTimer t_(ST_MOE_DOWN, s, timed);
-    TRI_HIP(planes(act, P, Fe, 0, a3));
-    TRI_HIP(planes(w->w_down, (int64_t)E * H, Fe, 1, wd3));
+    TRI_HIP(planes(act, P, Fe, a3));
     TRI_HIP(launch_gemm_grouped(a3, 3 * Fe, P, nullptr, k, wd3, (int64_t)H * 3 * Fe, H, 3 * Fe,
                                 seg, tile_off, E, P, e, s));
   }

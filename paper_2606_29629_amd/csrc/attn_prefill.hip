@@ -405,6 +405,12 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void attn_prefill_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) o4[e] = (E)(oacc[b][4 * r4 + e] * inv);
       *(E4*)(op + 32 * b + 8 * r4 + 4 * lg) = o4;
+      if constexpr (F32) {  // the O projection's operand planes
+        const int HD = Hq * D, col = qh * D + 32 * b + 8 * r4 + 4 * lg;
+        if (part)
+          split_planes4(f32x4{o4[0], o4[1], o4[2], o4[3]}, 0,
+                        (bf16*)part + (int64_t)(q0 + qi) * 3 * HD + col, HD);
+      }
     }
 }
 
@@ -525,10 +531,10 @@ hipError_t launch_attn_prefill(const void* q, const void* kc, const void* vc, vo
   if (f32) {  // fp32 storage: no key-range split
     const int H = n_q_heads, G = n_kv_heads, I = include_single;
     if (head_dim == 128)
-      return paged ? run_fa<128, true, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, nullptr, s)
-                   : run_fa<128, false, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, nullptr, s);
-    return paged ? run_fa<64, true, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, nullptr, s)
-                 : run_fa<64, false, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, nullptr, s);
+      return paged ? run_fa<128, true, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, part, s)
+                   : run_fa<128, false, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, part, s);
+    return paged ? run_fa<64, true, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, part, s)
+                 : run_fa<64, false, false, true>(q, kc, vc, out, b, kv, H, G, I, 1, part, s);
   }
   if (head_dim == 128)
     return paged ? run_fa_any<128, true>(q, kc, vc, out, b, kv, n_q_heads, n_kv_heads, include_single, part, s)

@@ -142,6 +142,26 @@ __device__ __forceinline__ void split_hilo8(const float (&p)[8], bf16x8& hi, bf1
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
+// bf16 operand planes of fp32 values (fp32 storage mode): each value v splits
+// into hi = bf16(v) and lo = bf16(v - hi) (the difference exact in fp32; hi + lo
+// keeps ~16 significant bits of v), and a row of `cols` values becomes three
+// planes of the row: pattern 0 [hi | lo | hi] (activations), pattern 1 [hi | hi |
+// lo] (weights).  A product of a pattern-0 row and a pattern-1 row over 3 cols
+// is a_hi b_hi + a_lo b_hi + a_hi b_lo: the fp32 product up to the a_lo b_lo term
+// and the splits' rounding (2^-16 relative).  o: the four values' place in the
+// first plane.
+__device__ __forceinline__ void split_planes4(f32x4 v, int pattern, bf16* __restrict__ o, int cols) {
+  bf16x4 hi, lo;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    hi[e] = f2bf(v[e]);
+    lo[e] = f2bf(v[e] - bf2f(hi[e]));
+  }
+  *(bf16x4*)o = hi;
+  *(bf16x4*)(o + cols) = pattern == 0 ? lo : hi;
+  *(bf16x4*)(o + 2 * (int64_t)cols) = pattern == 0 ? hi : lo;
+}
+
 // Balanced reductions of a lane's values.  A dependent VALU result takes tens
 // of cycles to come back, so a linear fold over n values is an n-deep
 // latency chain; a tree is log2(n) deep.

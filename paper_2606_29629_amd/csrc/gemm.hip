@@ -1440,20 +1440,21 @@ static int tail_tiles(int total) {
 
 constexpr int kMaxTailSplit = 8;  // K-parts of a tail tile, at most
 
-// How a bf16 GEMM of M x N x K runs: on 256 x 256 tiles, the last partial
-// round of them whole (split 1), in `split` K-parts, or as 128-row halves
-// (split 0), or on 128 x 256 or 128 x 128 tiles throughout.  The choice is
+// How a GEMM of M x N x K runs: on 256 x 256 tiles, the last partial round of
+// them whole (split 1), in `split` K-parts, or as 128-row halves (split 0), or
+// on 128 x 256 tiles, or on 128 x 128 tiles, all of them split in K where they
+// would fill less than half of the CUs.  The choice is
 // the least of the forms' estimated times: rounds of workgroups (one per CU)
 // of KT k-tiles, plus per round the fill and the epilogue, plus for a K-split
 // the partials written and read back and one more launch.  The constants are
 // measured at clocks the small GEMMs hold (per k-tile: 256 x 256 1.05 us, 128 x
-// 256 0.74 us, 128 x 128 0.55 us; they are bound by LDS, 256, 176 and 128 KB a
+// 256 0.74 us, 128 x 128 0.60 us; they are bound by LDS, 256, 176 and 128 KB a
 // k-tile through 128 B per clock, so the largest tile does the most per CU
 // and the small ones only pay where they fill more of the CUs).
 struct GemmPlan {
   int bm, bn, split;
 };
-constexpr float kUs256 = 1.05f, kUs128x256 = 0.74f, kUs128 = 0.55f;  // us per k-tile
+constexpr float kUs256 = 1.05f, kUs128x256 = 0.74f, kUs128 = 0.60f;  // us per k-tile
 constexpr float kUsRound256 = 12.f, kUsRound128x256 = 8.f, kUsRound128 = 6.f;  // us per round
 constexpr float kUsLaunch = 5.f;         // one more launch
 constexpr float kPartialMbPerUs = 4.2f;  // fp32 partials, written or read
@@ -1479,28 +1480,18 @@ static GemmPlan gemm_plan(int M, int N, int K, int kind, bool have_tail) {
     if (have_tail && !swiglu)
       for (int t = 2; t <= kMaxTailSplit && t * rem <= G && (t - 1) * cdiv(kt, t) < kt; ++t)
         offer(rounds + cdiv(kt, t) * kUs256 + kUsRound256 + 2 * kUsLaunch +
-                  2 * rem * t * 0.262f / kPartialMbPerUs,
+                  2 * rem * t * 0.262f * M / (cdiv(M, 256) * 256) / kPartialMbPerUs,
               {256, 256, t});
   }
   offer(cdiv(cdiv(M, 128) * cols256, G) * (kt * kUs128x256 + kUsRound128x256), {128, 256, 1});
-  if (!swiglu)
-    offer(cdiv(cdiv(M, 128) * cdiv(N, 128), G) * (kt * kUs128 + kUsRound128), {128, 128, 1});
+  const int t128 = cdiv(M, 128) * cdiv(N, 128);
+  offer(cdiv(t128, G) * (kt * kUs128 + kUsRound128), {128, 128, 1});
+  if (have_tail && !swiglu)
+    for (int t = 2; t <= kMaxTailSplit && t * t128 <= G && (t - 1) * cdiv(kt, t) < kt; ++t)
+      offer(cdiv(kt, t) * kUs128 + kUsRound128 + 2 * kUsLaunch +
+                2 * t128 * t * 0.0655f * M / (cdiv(M, 128) * 128) / kPartialMbPerUs,
+            {128, 128, t});
   return best;
-}
-
-// The K-split of the fp32 storage mode's tail tiles (and of fp32 outputs): as
-// many parts as fill the round.
-static int tail_split(int total, int K, int kind) {
-  const int G = cu_count();
-  const int rem = tail_tiles(total);
-  if (kind == EPI_SWIGLU || rem == 0) return 1;
-  // Split s covers k-tiles [s c, s c + c) with c = ceil(k-tiles / t), the
-  // last one the remainder: every split must keep at least one k-tile.
-  const int kt = K / kBK;
-  int t = G / rem;
-  if (t > kMaxTailSplit) t = kMaxTailSplit;
-  while (t > 1 && (t - 1) * cdiv(kt, t) >= kt) --t;
-  return t;
 }
 
 // Bound for every large GEMM: the tail tiles times their splits never exceed
@@ -1659,26 +1650,26 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int EK, int SH = 32>
+template <int BM, int BN, int WGM, int WGN, int EK, int S, int SH>
 static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, int M, int N,
                                 int K, const Epi& epi, float* tail, hipStream_t s, int t) {
   constexpr int KIND = EK & kEpiKindMask;
   const int tiles_m = cdiv(M, BM);
   const int tiles_n = KIND == EPI_SWIGLU ? cdiv(epi.ffn, BN / 2) : cdiv(N, BN);
   const int total = tiles_m * tiles_n;
-  if (t == 1) return run_gemm<BM, BN, WGM, WGN, EK, 2, SH>(A, lda, B, ldb, M, N, K, epi, s);
+  if (t == 1) return run_gemm<BM, BN, WGM, WGN, EK, S, SH>(A, lda, B, ldb, M, N, K, epi, s);
   const int n_tail = tail_tiles(total);
   const int full = total - n_tail;
-  const size_t smem = sizeof(GemmSmem<BM, BN>);
+  const size_t smem = sizeof(GemmSmem<BM, BN, S>);
   static bool attr_set = false;
-  hipError_t e = opt_in_lds(gemm_kernel<BM, BN, WGM, WGN, EK, 2, SH>, smem, attr_set);
+  hipError_t e = opt_in_lds(gemm_kernel<BM, BN, WGM, WGN, EK, S, SH>, smem, attr_set);
   if (e != hipSuccess) return e;
   // t = 0: the tail tiles run as a second launch of their 128-row halves over
   // the whole K, with no fp32 partials and no reduction kernel.
-  if constexpr (BM == 256 && BN == 256 && !(EK & kEpiF32) && KIND != EPI_STORE_F32) {
+  if constexpr (BM == 256) {
     if (t == 0) {
       if (full > 0) {
-        gemm_kernel<BM, BN, WGM, WGN, EK, 2, SH><<<full, WGM * WGN * 64, smem, s>>>(
+        gemm_kernel<BM, BN, WGM, WGN, EK, S, SH><<<full, WGM * WGN * 64, smem, s>>>(
             (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, K, epi, tiles_m, tiles_n, full, 1,
             nullptr);
         e = hipGetLastError();
@@ -1695,7 +1686,7 @@ static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, 
     }
   }
   if (KIND == EPI_SWIGLU) return hipErrorInvalidValue;  // (its tail is never split in K)
-  gemm_kernel<BM, BN, WGM, WGN, EK, 2, SH><<<full + n_tail * t, WGM * WGN * 64, smem, s>>>(
+  gemm_kernel<BM, BN, WGM, WGN, EK, S, SH><<<full + n_tail * t, WGM * WGN * 64, smem, s>>>(
       (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, K, epi, tiles_m, tiles_n, full, t, tail);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1713,39 +1704,25 @@ static hipError_t run_planned(const void* A, int lda, const void* B, int ldb, in
   constexpr int KIND = EK & kEpiKindMask;
   const GemmPlan p = gemm_plan(M, KIND == EPI_SWIGLU ? 2 * epi.ffn : N, K, KIND, tail != nullptr);
   if (p.bm == 256)
-    return run_gemm_tail<256, 256, 2, 4, EK, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s,
-                                                         p.split);
-  if constexpr (KIND != EPI_SWIGLU) {
-    if (p.bn == 128)
-      return run_gemm<128, 128, 2, 4, EK, 5, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-  }
-  return run_gemm<128, 256, 2, 4, EK, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-}
-
-// fp32 storage and fp32 outputs: 256 x 256 tiles, the tail split in K.
-template <int EK>
-static hipError_t run_tail_split(const void* A, int lda, const void* B, int ldb, int M, int N,
-                                 int K, const Epi& epi, float* tail, hipStream_t s) {
-  constexpr int KIND = EK & kEpiKindMask;
-  const int n = KIND == EPI_SWIGLU ? cdiv(epi.ffn, 128) : cdiv(N, 256);
-  const int t = tail ? tail_split(cdiv(M, 256) * n, K, KIND) : 1;
-  return run_gemm_tail<256, 256, 2, 4, EK, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s, t);
+    return run_gemm_tail<256, 256, 2, 4, EK, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s,
+                                                            p.split);
+  if (p.bn == 256)
+    return run_gemm<128, 256, 2, 4, EK, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
+  return run_gemm_tail<128, 128, 2, 4, EK, 5, kMidSH>(A, lda, B, ldb, M, N, K, epi, tail, s, p.split);
 }
 
 hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                        const Epi& epi, float* tail, hipStream_t s) {
   if (M == 0) return hipSuccess;
-  if (epi.kind == EPI_STORE_F32)
-    return run_tail_split<EPI_STORE_F32>(A, lda, B, ldb, M, N, K, epi, tail, s);
   if (epi.f32) {
     constexpr int F = kEpiF32;
     switch (epi.kind) {
-      case EPI_RESID: return run_tail_split<EPI_RESID | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
-      case EPI_SWIGLU: return run_tail_split<EPI_SWIGLU | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      case EPI_RESID: return run_planned<EPI_RESID | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
+      case EPI_SWIGLU: return run_planned<EPI_SWIGLU | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
       case EPI_QKV:
         if (epi.q_norm)
-          return run_tail_split<EPI_QKV_NORM | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
-        return run_tail_split<EPI_QKV | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
+          return run_planned<EPI_QKV_NORM | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
+        return run_planned<EPI_QKV | F>(A, lda, B, ldb, M, N, K, epi, tail, s);
       default: return hipErrorInvalidValue;
     }
   }
@@ -1753,6 +1730,7 @@ hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, in
     case EPI_STORE: return run_planned<EPI_STORE>(A, lda, B, ldb, M, N, K, epi, tail, s);
     case EPI_RESID: return run_planned<EPI_RESID>(A, lda, B, ldb, M, N, K, epi, tail, s);
     case EPI_SWIGLU: return run_planned<EPI_SWIGLU>(A, lda, B, ldb, M, N, K, epi, tail, s);
+    case EPI_STORE_F32: return hipErrorInvalidValue;
     default:
       if (epi.q_norm) return run_planned<EPI_QKV_NORM>(A, lda, B, ldb, M, N, K, epi, tail, s);
       return run_planned<EPI_QKV>(A, lda, B, ldb, M, N, K, epi, tail, s);

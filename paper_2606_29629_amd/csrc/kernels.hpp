@@ -80,23 +80,34 @@ struct RopeSections {
 // token, -1 when out of range), the rotary table rope[t][i] = (cos, sin)(p *
 // base^(-2i/D)) with p the token's position in frequency i's section (angle in
 // double precision), and y = RMSNorm(x) * g.
-// x, g, y are bf16, or fp32 with f32 (the fp32 storage mode).
+// x, g, y are bf16, or fp32 with f32 (the fp32 storage mode), which also writes
+// y's operand planes [n_tokens, 3 hidden] to planes when given.
 hipError_t launch_prologue(const BatchDev& b, const KvDev& kv, int head_dim, float rope_base,
                            RopeSections sec, int32_t* tok_slot, int32_t* tok_row, float2* rope,
                            const void* x, const void* g, void* y, int hidden, float eps,
-                           hipStream_t s, bool f32 = false);
+                           hipStream_t s, bool f32 = false, void* planes = nullptr);
 
 // y = x / sqrt(mean(x^2) + eps) * g   (bf16 out with an optional fp32 copy, or
 // fp32 in and out with f32)
 hipError_t launch_rmsnorm(const void* x, const void* g, void* y, float* y32, int rows,
-                          int hidden, float eps, hipStream_t s, bool f32 = false);
+                          int hidden, float eps, hipStream_t s, bool f32 = false,
+                          void* planes = nullptr);
 
-// bf16 planes of an fp32 matrix [rows, cols] (row stride ld_in) for the
-// matrix cores: out [rows, 3 cols] = [hi | lo | hi] (pattern 0, activations)
-// or [hi | hi | lo] (pattern 1, weights), hi = bf16(v), lo = bf16(v - hi);
-// cols is a multiple of 4.
-hipError_t launch_split3(const float* in, int64_t ld_in, int64_t rows, int cols, int pattern,
-                         void* out, hipStream_t s);
+// bf16 planes of fp32 matrices [rows, cols] for the matrix cores: out [rows,
+// 3 cols] = [hi | lo | hi] (pattern 0, activations) or [hi | hi | lo] (pattern 1,
+// weights), hi = bf16(v), lo = bf16(v - hi); cols is a multiple of 4.
+constexpr int kMaxSplit3 = 4;
+struct Split3Job {
+  const float* in;
+  int64_t rows;
+  int cols, pattern;
+  void* out;
+};
+struct Split3Jobs {
+  int n;
+  Split3Job job[kMaxSplit3];
+};
+hipError_t launch_split3(const Split3Jobs& jobs, hipStream_t s);
 
 // KV append for a batch given by its device arrays: cache row ctx_len[s] + i
 // of slot slot[s] (through the block table when paged) <- row t of k_new /
@@ -157,8 +168,9 @@ int attn_prefill_splits(int n_seqs, int n_tokens, int max_q_len, int max_ctx_len
                         int n_q_heads);
 size_t attn_prefill_partial_bytes(int n_seqs, int n_tokens, int max_q_len, int max_ctx_len,
                                   int n_q_heads, int head_dim);
-// With f32 (the fp32 storage mode) q, the cache and out are fp32 and the key
-// range is not split.
+// With f32 (the fp32 storage mode) q, the cache and out are fp32, the key range
+// is not split, and out's operand planes [n_tokens, 3 Hq D] go to part when
+// given.
 hipError_t launch_attn_prefill(const void* q, const void* kc, const void* vc, void* out,
                                const BatchDev& b, const KvDev& kv, int n_q_heads,
                                int n_kv_heads, int head_dim, int include_single, float* part,

@@ -11,11 +11,12 @@ namespace tri {
 constexpr int kNormMaxChunks = 16;  // hidden <= 64 lanes * 8 * 16 = 8192
 
 // fp32 storage: y = x / sqrt(mean(x^2) + eps) * g over one row, a wave per
-// row in two passes (sum of squares, then the scaled product).
+// row in two passes (sum of squares, then the scaled product).  planes: nullable,
+// the row's operand planes [3 hidden].
 __device__ __forceinline__ void rmsnorm_row_f32(const float* __restrict__ xr,
                                                 const float* __restrict__ g,
                                                 float* __restrict__ yr, int hidden, float eps,
-                                                int lane) {
+                                                int lane, bf16* __restrict__ planes) {
   float ss = 0.f;
   for (int i = 4 * lane; i < hidden; i += 256) {
     const f32x4 v = *(const f32x4*)(xr + i);
@@ -25,8 +26,9 @@ __device__ __forceinline__ void rmsnorm_row_f32(const float* __restrict__ xr,
   const float r = 1.0f / sqrtf(ss / (float)hidden + eps);
   for (int i = 4 * lane; i < hidden; i += 256) {
     const f32x4 v = *(const f32x4*)(xr + i), gv = *(const f32x4*)(g + i);
-    *(f32x4*)(yr + i) = f32x4{v[0] * r * gv[0], v[1] * r * gv[1], v[2] * r * gv[2],
-                              v[3] * r * gv[3]};
+    const f32x4 y = f32x4{v[0] * r * gv[0], v[1] * r * gv[1], v[2] * r * gv[2], v[3] * r * gv[3]};
+    *(f32x4*)(yr + i) = y;
+    if (planes) split_planes4(y, 0, planes + i, hidden);
   }
 }
 
@@ -35,13 +37,15 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
                                                       const void* __restrict__ gv_,
                                                       void* __restrict__ yv,
                                                       float* __restrict__ y32, int rows,
-                                                      int hidden, float eps) {
+                                                      int hidden, float eps,
+                                                      bf16* __restrict__ planes) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   if constexpr (F32) {
     rmsnorm_row_f32((const float*)xv + (int64_t)row * hidden, (const float*)gv_,
-                    (float*)yv + (int64_t)row * hidden, hidden, eps, lane);
+                    (float*)yv + (int64_t)row * hidden, hidden, eps, lane,
+                    planes ? planes + (int64_t)row * 3 * hidden : nullptr);
     return;
   }
   const bf16* __restrict__ x = (const bf16*)xv;
@@ -95,12 +99,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
 }
 
 hipError_t launch_rmsnorm(const void* x, const void* g, void* y, float* y32, int rows, int hidden,
-                          float eps, hipStream_t s, bool f32) {
+                          float eps, hipStream_t s, bool f32, void* planes) {
   if (rows == 0) return hipSuccess;
   if (f32)
-    rmsnorm_kernel<true><<<cdiv(rows, 4), 256, 0, s>>>(x, g, y, nullptr, rows, hidden, eps);
+    rmsnorm_kernel<true><<<cdiv(rows, 4), 256, 0, s>>>(x, g, y, nullptr, rows, hidden, eps,
+                                                       (bf16*)planes);
   else
-    rmsnorm_kernel<false><<<cdiv(rows, 4), 256, 0, s>>>(x, g, y, y32, rows, hidden, eps);
+    rmsnorm_kernel<false><<<cdiv(rows, 4), 256, 0, s>>>(x, g, y, y32, rows, hidden, eps, nullptr);
   return hipGetLastError();
 }
 
@@ -125,7 +130,7 @@ __global__ __launch_bounds__(256) void prologue_kernel(BatchDev b, KvDev kv, int
                                                        const void* __restrict__ xv,
                                                        const void* __restrict__ gv_,
                                                        void* __restrict__ yv, int hidden,
-                                                       float eps) {
+                                                       float eps, bf16* __restrict__ planes) {
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= b.n_tokens) return;
@@ -176,7 +181,8 @@ __global__ __launch_bounds__(256) void prologue_kernel(BatchDev b, KvDev kv, int
   }
   if constexpr (F32) {
     rmsnorm_row_f32((const float*)xv + (int64_t)t * hidden, (const float*)gv_,
-                    (float*)yv + (int64_t)t * hidden, hidden, eps, lane);
+                    (float*)yv + (int64_t)t * hidden, hidden, eps, lane,
+                    planes ? planes + (int64_t)t * 3 * hidden : nullptr);
   } else {
     float ss = 0.f;
 #pragma unroll
@@ -217,16 +223,16 @@ __global__ __launch_bounds__(256) void prologue_kernel(BatchDev b, KvDev kv, int
 hipError_t launch_prologue(const BatchDev& b, const KvDev& kv, int head_dim, float rope_base,
                            RopeSections sec, int32_t* tok_slot, int32_t* tok_row, float2* rope,
                            const void* x, const void* g, void* y, int hidden, float eps,
-                           hipStream_t s, bool f32) {
+                           hipStream_t s, bool f32, void* planes) {
   if (b.n_tokens == 0) return hipSuccess;
   if (f32)
     prologue_kernel<true><<<cdiv(b.n_tokens, 4), 256, 0, s>>>(
         b, kv, head_dim / 2, (double)rope_base, sec, tok_slot, tok_row, rope, x, g, y, hidden,
-        eps);
+        eps, (bf16*)planes);
   else
     prologue_kernel<false><<<cdiv(b.n_tokens, 4), 256, 0, s>>>(
         b, kv, head_dim / 2, (double)rope_base, sec, tok_slot, tok_row, rope, x, g, y, hidden,
-        eps);
+        eps, nullptr);
   return hipGetLastError();
 }
 
@@ -275,42 +281,33 @@ hipError_t launch_kv_append_direct(const BatchDev& b, const KvDev& kv, int n_kv_
   return hipGetLastError();
 }
 
-// bf16 operand planes of an fp32 matrix for the matrix cores (fp32 storage
-// mode): each value v splits into hi = bf16(v) and lo = bf16(v - hi) (the
-// difference exact in fp32; hi + lo keeps ~16 significant bits of v), and
-// row r of the output [rows, 3 cols] holds three planes of the row: pattern
-// 0 [hi | lo | hi], pattern 1 [hi | hi | lo].  A product of a pattern-0 row
-// and a pattern-1 row over 3 cols is a_hi b_hi + a_lo b_hi + a_hi b_lo: the
-// fp32 product up to the a_lo b_lo term and the splits' rounding (2^-16
-// relative).  One thread per 4 values; cols is a multiple of 4, ld_in the
-// input row stride.
-__global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ in, int64_t ld_in,
-                                                     int64_t rows, int cols, int pattern,
-                                                     bf16* __restrict__ out) {
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int q = cols / 4;
-  if (gid >= rows * q) return;
-  const int64_t r = gid / q;
-  const int c = (int)(gid - r * q) * 4;
-  const f32x4 v = *(const f32x4*)(in + r * ld_in + c);
-  bf16x4 hi, lo;
+// bf16 operand planes of fp32 matrices for the matrix cores (fp32 storage
+// mode): see split_planes4; one thread per 4 values, up to kMaxSplit3 matrices
+// (a layer's weights) in one launch.
+__global__ __launch_bounds__(256) void split3_kernel(Split3Jobs jobs) {
+  int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // (the job list is walked with constant indices: it stays in registers)
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    hi[e] = f2bf(v[e]);
-    lo[e] = f2bf(v[e] - bf2f(hi[e]));
+  for (int k = 0; k < kMaxSplit3; ++k) {
+    const Split3Job& j = jobs.job[k];
+    const int q = j.cols / 4;
+    const int64_t n = k < jobs.n ? j.rows * q : 0;
+    if (gid < n) {
+      const int64_t r = gid / q;
+      const int c = (int)(gid - r * q) * 4;
+      split_planes4(*(const f32x4*)(j.in + r * j.cols + c), j.pattern,
+                    (bf16*)j.out + r * 3 * (int64_t)j.cols + c, j.cols);
+      return;
+    }
+    gid -= n;
   }
-  bf16* o = out + r * 3 * (int64_t)cols + c;
-  *(bf16x4*)o = hi;
-  *(bf16x4*)(o + cols) = pattern == 0 ? lo : hi;
-  *(bf16x4*)(o + 2 * cols) = pattern == 0 ? hi : lo;
 }
 
-hipError_t launch_split3(const float* in, int64_t ld_in, int64_t rows, int cols, int pattern,
-                         void* out, hipStream_t s) {
-  const int64_t n = rows * (cols / 4);
+hipError_t launch_split3(const Split3Jobs& jobs, hipStream_t s) {
+  int64_t n = 0;
+  for (int k = 0; k < jobs.n; ++k) n += jobs.job[k].rows * (jobs.job[k].cols / 4);
   if (n == 0) return hipSuccess;
-  split3_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(in, ld_in, rows, cols, pattern,
-                                                            (bf16*)out);
+  split3_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(jobs);
   return hipGetLastError();
 }
 

@@ -27,6 +27,7 @@ PING = [
 ]
 MID = [
     (1061, 768, 9472),   # 256 x 256 tiles split in K, 37 valid rows in the last (partials of those only)
+    (300, 516, 4096),    # 128 x 128 tiles split in K, 44 valid rows and 4 columns in the last
     (900, 1280, 2048),   # 128 x 128 tiles, 4 valid rows in the last
     (1400, 4352, 512),   # 128 x 256 tiles
     (200, 700, 256),     # 128 x 128 tiles, rows of 1400 bytes
