@@ -384,8 +384,9 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(
 // GS: the group's (m, l, acc) loads are issued together, then folded in split
 // order into a running (M, L, o).  GS = 8 serves the few splits of a full
 // batch; a small batch over long contexts has up to 64, where each group of
-// eight cost a memory round trip (40 splits, one sequence: 8.6 us), so it takes
-// them 32 at a time.
+// eight cost a memory round trip (40 splits, one sequence: 10.7 us, 8.5 us taken
+// 32 at a time).  Up to 16 the two groups of eight are the faster (23 sequences
+// of 100 to 8000 tokens: 7.3 against 7.8 us).
 template <int D, int GS>
 __global__ __launch_bounds__(128) void attn_combine_kernel(
     const float* __restrict__ part, bf16* __restrict__ O, const int32_t* __restrict__ cu_q,
@@ -397,16 +398,22 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(
   if (sl < 0 || sl >= n_slots || c < 0 || c + 1 > max_seq) return;
   const int ns = min(cdiv(c + 1, split_keys), nsplit);  // never past the launched splits
   const float* pp = part + ((int64_t)s * Hq + qh) * nsplit * (D + 2);
+  // (GS = 32: m and l have the same address in every lane, yet take vector loads:
+  // 64 scalar results in flight spill scalar registers, 8.2 against 7.2 us)
+  int zero = 0;
+  if constexpr (GS > 8) asm("" : "+v"(zero));
   float M = -INFINITY, Lsum = 0.f, o = 0.f;
   for (int i0 = 0; i0 < ns; i0 += GS) {
     float m[GS], l[GS], a[GS];
 #pragma unroll
     for (int j = 0; j < GS; ++j) {
-      // (past the last split: the last one again, dropped)
-      const float* q = pp + min(i0 + j, ns - 1) * (D + 2);
-      m[j] = q[D];
-      l[j] = q[D + 1];
-      a[j] = q[d];
+      // GS = 8 skips the splits past the last one; 32 loads the last one again
+      // (dropped below), with no branch between the loads
+      const bool ok = GS > 8 || i0 + j < ns;
+      const float* q = pp + (GS > 8 ? min(i0 + j, ns - 1) : (ok ? i0 + j : 0)) * (D + 2);
+      m[j] = ok ? q[D + zero] : -INFINITY;
+      l[j] = ok ? q[D + 1 + zero] : 0.f;
+      a[j] = ok ? q[d] : 0.f;
     }
 #pragma unroll
     for (int j = 0; j < GS; ++j) {
@@ -464,7 +471,7 @@ hipError_t launch_attn_decode_combine(const float* part, void* out, const BatchD
     kernel<<<cgrid, head_dim, 0, s>>>(part, (bf16*)out, b.cu_q, b.ctx_len, b.slot, n_slots, max_seq,
                                       n_q_heads, nsplit, split, b.n_tokens);
   };
-  const bool many = nsplit > 8;
+  const bool many = nsplit > 16;
   if (head_dim == 128) run(many ? attn_combine_kernel<128, 32> : attn_combine_kernel<128, 8>);
   else run(many ? attn_combine_kernel<64, 32> : attn_combine_kernel<64, 8>);
   return hipGetLastError();
