@@ -595,6 +595,7 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
   e.n_kv_heads = Hkv;
   e.head_dim = D;
   e.max_seq = kv.panel_rows();
+  e.routed = moe;
   {
     StageTimer t_(ST_QKV, s, timed);
     if ((st = run_linear(h, H, w->w_qkv, T, Nqkv, H, e, part, s)) != TRI_OK) return st;
@@ -642,6 +643,7 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
   e.ldo = H;
   e.resid = x_in;
   e.ldr = H;
+  e.routed = moe;
   // A few rows: gate/up normalises x1 itself (no norm launch at all).
   const bool norm_in_gate_up =
       !moe && stream_norm_ok(T, H) && skinny_resid_norm_fused(T, H, Hq * D);

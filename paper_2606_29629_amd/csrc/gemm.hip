@@ -968,8 +968,8 @@ __device__ __forceinline__ void swiglu_epilogue(const typename Mfma<SH>::acc_t (
 // QB consecutive first-half groups g0 .. g0 + QB - 1 of row block i, all in
 // one q (KIND 0), k (1) or v (2) head: the lane's token row, head-dim values
 // d + (col(g0 + u) - col(g0)) + e of the first half and the same plus D / 2
-// from group g0 + u + GH.
-template <int KIND, int SH, int MI, int NI, int GH, int QB, bool F32, int RH = 0>
+// from group g0 + u + GH.  NRM: the values are normalised and have their bias.
+template <int KIND, int SH, int MI, int NI, int GH, int QB, bool F32, int RH = 0, bool NRM = false>
 __device__ __forceinline__ void qkv_block(const typename Mfma<SH>::acc_t (&acc)[MI][NI],
                                           const Epi& epi, int i, int g0, int D, int row0, int M,
                                           int head, int d, const float (&b1)[QB][4],
@@ -1011,11 +1011,13 @@ __device__ __forceinline__ void qkv_block(const typename Mfma<SH>::acc_t (&acc)[
     const f32x4 v1 = Geo::grp(acc, i, g0 + u), v2 = Geo::grp(acc, i, g0 + u + GH);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float x1 = v1[e] + b1[u][e], x2 = v2[e] + b2[u][e];
+      float x1 = NRM ? v1[e] : v1[e] + b1[u][e], x2 = NRM ? v2[e] : v2[e] + b2[u][e];
       if constexpr (KIND != 2) {
         const float c = cs[u][e >> 1][2 * (e & 1)], sn = cs[u][e >> 1][2 * (e & 1) + 1];
-        const float y1 = x1 * c - x2 * sn;
-        const float y2 = x2 * c + x1 * sn;
+        // (the fused multiply-adds are written out: which product of a sum is
+        // rounded is otherwise the compiler's choice in each instantiation)
+        const float y1 = fmaf(x1, c, -(x2 * sn));
+        const float y2 = NRM ? fmaf(x2, c, x1 * sn) : fmaf(x1, sn, x2 * c);
         x1 = y1;
         x2 = y2;
       }
@@ -1068,7 +1070,6 @@ __device__ __forceinline__ void qkv_ping_rows(typename ML::acc_t (&acc)[ML::MI][
   constexpr bool NRM = NORM && KIND != 2;
   const int D = epi.head_dim, lr = threadIdx.x & 15;
   const int wph = D / ML::WC;  // waves that share a head: 1, 2 or 4
-  const float z[HB][4] = {};
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     if constexpr (NRM) {
@@ -1088,7 +1089,7 @@ __device__ __forceinline__ void qkv_ping_rows(typename ML::acc_t (&acc)[ML::MI][
           acc[i][u + HB][e] = (acc[i][u + HB][e] + b2[u][e]) * (r * g2[e]);
         }
       }
-      qkv_block<KIND, SH, MI, NI, HB, HB, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, z, z);
+      qkv_block<KIND, SH, MI, NI, HB, HB, F32, RH, true>(acc, epi, i, 0, D, row0, M, head, d, b1, b2);
     } else {
       qkv_block<KIND, SH, MI, NI, HB, HB, F32, RH>(acc, epi, i, 0, D, row0, M, head, d, b1, b2);
     }
@@ -1128,16 +1129,22 @@ __device__ __forceinline__ void qkv_ping_epilogue(typename ML::acc_t (&acc)[ML::
     }
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      float ss = 0.f;
+      // by four columns, then lanes, then groups (waves below): a tree that is
+      // the same for every tile form
+      float su[HB];
 #pragma unroll
-      for (int u = 0; u < HB; ++u)
+      for (int u = 0; u < HB; ++u) {
+        su[u] = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float x1 = acc[i][u][e] + b1[u][e], x2 = acc[i][u + HB][e] + b2[u][e];
-          ss += x1 * x1 + x2 * x2;
+          su[u] += x1 * x1 + x2 * x2;
         }
-      ss += __shfl_xor(ss, 16, 64);
-      ss += __shfl_xor(ss, 32, 64);
+        su[u] += __shfl_xor(su[u], 16, 64);
+        su[u] += __shfl_xor(su[u], 32, 64);
+      }
+      static_assert(HB == 1 || HB == 2, "a wave's first-half groups of a head");
+      const float ss = HB == 2 ? su[0] + su[HB - 1] : su[0];
       if (lane < 16) sm.ss[wv][16 * i + lr] = ss;
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1459,7 +1466,7 @@ constexpr float kUsRound256 = 12.f, kUsRound128x256 = 8.f, kUsRound128 = 6.f;  /
 constexpr float kUsLaunch = 5.f;         // one more launch
 constexpr float kPartialMbPerUs = 4.2f;  // fp32 partials, written or read
 
-static GemmPlan gemm_plan(int M, int N, int K, int kind, bool have_tail) {
+static GemmPlan gemm_plan(int M, int N, int K, int kind, bool have_tail, bool routed) {
   const int G = cu_count(), kt = K / kBK;
   const int cols256 = cdiv(N, 256), t256 = cdiv(M, 256) * cols256;
   const bool swiglu = kind == EPI_SWIGLU;
@@ -1473,6 +1480,19 @@ static GemmPlan gemm_plan(int M, int N, int K, int kind, bool have_tail) {
   };
   const int rem = tail_tiles(t256);
   const float rounds = (t256 - rem) / G * (kt * kUs256 + kUsRound256);
+  // The rows of a mixture of experts go on to its router, where a near tie
+  // makes another sum order another choice of experts (measured: about one
+  // token in 2000, a tenth of the rms in its output).  There K is cut only
+  // where a last round holds less than a fifth of the chip's tiles (a quarter
+  // with a long K); whole tiles sum in the same order whatever their form.
+  if (routed && have_tail) {
+    if (rem > 0 && (t256 > G || K > 8192)) {
+      int t = min(G / rem, kMaxTailSplit);
+      while (t > 1 && (t - 1) * cdiv(kt, t) >= kt) --t;
+      if (t > 4 || (t == 4 && K > 4096)) return {256, 256, t};
+    }
+    have_tail = false;
+  }
   if (rem > 0) {
     offer(rounds + cdiv(2 * rem, G) * (kt * kUs128x256 + kUsRound128x256) +
               (t256 > rem ? kUsLaunch : 0.f),
@@ -1702,7 +1722,8 @@ template <int EK>
 static hipError_t run_planned(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                               const Epi& epi, float* tail, hipStream_t s) {
   constexpr int KIND = EK & kEpiKindMask;
-  const GemmPlan p = gemm_plan(M, KIND == EPI_SWIGLU ? 2 * epi.ffn : N, K, KIND, tail != nullptr);
+  const GemmPlan p = gemm_plan(M, KIND == EPI_SWIGLU ? 2 * epi.ffn : N, K, KIND, tail != nullptr,
+                               epi.routed != 0);
   if (p.bm == 256)
     return run_gemm_tail<256, 256, 2, 4, EK, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s,
                                                             p.split);

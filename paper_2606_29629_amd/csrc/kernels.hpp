@@ -68,6 +68,7 @@ struct Epi {
   const void* k_norm;
   float eps;                // their epsilon
   int n_q_heads, n_kv_heads, head_dim, max_seq;
+  int routed;  // 1: the rows go on to a router (bf16): the sum over K is not cut for speed alone
 };
 
 // Rotary frequency sections: frequency i < s0 takes position plane 0
