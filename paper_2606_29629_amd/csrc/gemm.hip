@@ -1,4 +1,4 @@
-// Prefill GEMMs on the matrix cores: C[M,N] = A[M,K] B[N,K]^T, bf16 operands,
+// GEMMs on the matrix cores: C[M,N] = A[M,K] B[N,K]^T, bf16 operands,
 // fp32 accumulation, with the layer's epilogues fused (residual add, SwiGLU,
 // q/k/v split + rotary embedding + KV-cache write, fp32 store).
 //
@@ -8,16 +8,15 @@
 // k 8 (l / 32) .. + 7, in v_mfma_f32_16x16x32_bf16 row l % 16 and k 8 (l / 16)
 // .. + 7.
 //
-// Tiling: BM x BN x 64 block tile, WGM x WGN waves (two waves per SIMD, so one
-// wave's LDS waits overlap the other's MFMAs), each wave a (BM/WGM) x (BN/WGN)
-// sub-tile of SH x SH MFMA blocks: 32x32x16 or 16x16x32 instructions (the
-// same flops per clock; the 16x16 form moves half the accumulator bytes per
-// flop through the register file, which lets the power-capped prefill GEMMs
-// hold a higher clock).  A and B tiles are staged through LDS, double
-// buffered, with 16-byte chunks XOR-swizzled (see swz) so that fragment reads
-// are free of bank conflicts.  Tiles move from HBM to LDS with
-// buffer_load_dwordx4 ... lds (no register staging); the loads of tile k+1
-// are in flight while the MFMAs of tile k run.
+// Tiling: BM x BN x 64 block tile, WGM x WGN waves, A and B tiles staged through
+// LDS with buffer_load_dwordx4 ... lds (no register staging), 16-byte chunks
+// XOR-swizzled (see swz) so that fragment reads are free of bank conflicts.
+// Two main loops: the large tiles (256 x 256, 128 x 256, 128 x 128 on
+// 16x16x32 MFMAs, which move half the accumulator bytes per flop through the
+// register file and so hold a higher clock under the power cap) run two groups
+// of waves half a phase apart, one group's reads under the other's MFMAs
+// (PingLoop, PingSmall); the decode tiles (64 and 32 rows, 32x32x16) keep one
+// barrier per k-tile, the loads of tile k+1 in flight while tile k computes.
 //
 // Dense kernel: workgroups are dispatched round-robin over the 8 XCDs; the
 // linear block id is remapped so each XCD owns a contiguous range of tiles,
@@ -1579,12 +1578,8 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
       const int e = e0 + 256 * q;
       const int row = tm * BM + e / BN, col = tn * BN + e % BN;
       if (e >= e_end || col >= N) continue;
-      if (epi.kind == EPI_STORE_F32) {
-        ((float*)epi.out)[(int64_t)row * epi.ldo + col] = v[q];
-      } else {
-        const float o = epi.kind == EPI_RESID ? v[q] + res[q] : v[q];
-        St::st(epi.out, (int64_t)row * epi.ldo + col, o);
-      }
+      const float o = epi.kind == EPI_RESID ? v[q] + res[q] : v[q];
+      St::st(epi.out, (int64_t)row * epi.ldo + col, o);
     }
     return;
   } else {
