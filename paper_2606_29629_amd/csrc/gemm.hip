@@ -2031,9 +2031,15 @@ static hipError_t run_skinny_planes(const void* A, int lda, const void* B, int l
   return run_gemm<64, kSkinnyBN, 2, 1, EPI_STORE_F32>(A, lda, B, ldb, M, N, K, pe, s, splits);
 }
 
-size_t skinny_partial_bytes(int M, int N, int K, int kind) {
+// Whether the projection runs as one fp32 plane finished by splitk_epi_kernel:
+// the q/k norm of a stream's few rows, which needs whole heads.
+static bool stream_norm_plane(int M, int kind, bool qk_norm) {
+  return M <= kStreamMaxRows && kind == EPI_QKV && qk_norm;
+}
+
+size_t skinny_partial_bytes(int M, int N, int K, int kind, bool qk_norm) {
   const int s = skinny_splits(M, N, K, kind);
-  return s > 1 ? (size_t)s * M * N * sizeof(float) : 0;
+  return s > 1 || stream_norm_plane(M, kind, qk_norm) ? (size_t)s * M * N * sizeof(float) : 0;
 }
 
 template <int BM, int WGM>
@@ -2072,8 +2078,8 @@ hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, 
                          const Epi& epi, float* part, hipStream_t s) {
   if (M == 0) return hipSuccess;
   if (M <= kStreamMaxRows) {
-    if (!(epi.kind == EPI_QKV && epi.q_norm)) return launch_stream(A, lda, B, ldb, M, N, K, epi, s);
-    // the q/k norm needs whole heads: one fp32 plane, finished row by row
+    if (!stream_norm_plane(M, epi.kind, epi.q_norm != nullptr))
+      return launch_stream(A, lda, B, ldb, M, N, K, epi, s);
     hipError_t e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
     if (e != hipSuccess) return e;
     const int64_t n = (int64_t)M * (epi.n_q_heads + 2 * epi.n_kv_heads) * (epi.head_dim / 2);

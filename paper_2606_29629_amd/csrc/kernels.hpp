@@ -140,7 +140,7 @@ bool skinny_resid_norm_fused(int M, int N, int K);
 hipError_t launch_skinny_resid_norm(const void* A, int lda, const void* B, int ldb, int M, int N,
                                     int K, const void* resid, int ldr, void* out, int ldo,
                                     const void* g, void* y, float eps, float* part, hipStream_t s);
-size_t skinny_partial_bytes(int M, int N, int K, int kind);
+size_t skinny_partial_bytes(int M, int N, int K, int kind, bool qk_norm = false);
 hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                          const Epi& epi, float* part, hipStream_t s);
 

@@ -388,7 +388,8 @@ def test_workspace_size_never_shrinks_as_tokens_grow(lib):
               n_experts=128, top_k=8, expert_ffn_dim=768, flags=T.TRI_F_MOE)
     shapes = (lambda n: batch(n_seqs=n, n_tokens=n, max_q=1, max_ctx=4096),  # decode steps
               lambda n: batch(n_seqs=1, n_tokens=n, max_q=n, max_ctx=0))     # one prompt
-    for c in (dense, moe):
+    odd = qk_norm_of_odd_hidden()[2]
+    for c in (dense, moe, odd):
         for shape in shapes:
             prev = 0
             for n in list(range(1, 300)) + [512, 1024, 4096]:
@@ -398,3 +399,27 @@ def test_workspace_size_never_shrinks_as_tokens_grow(lib):
                                               ctypes.byref(s)) == 0
                 assert s.value >= prev, (c.hidden, n, s.value, prev)
                 prev = s.value
+
+
+def qk_norm_of_odd_hidden():
+    """Layers with the q/k norm whose hidden size is an odd multiple of 64 (K is
+    not cut there, so no split-K planes are reserved)."""
+    return [cfg(hidden=h, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, ffn_dim=f,
+                flags=T.TRI_F_QK_NORM)
+            for h, hq, hkv, f in ((192, 3, 3, 320), (448, 7, 1, 192), (448, 7, 7, 1152),
+                                  (1472, 23, 23, 4160), (320, 5, 5, 64), (64, 1, 1, 64))]
+
+
+def test_workspace_holds_the_plane_of_a_normed_qkv_of_few_tokens(lib):
+    """Up to 16 tokens q, k and v pass through one fp32 plane [T, (Hq + 2 Hkv) D]
+    in the layer's last workspace region (after act) when q and k are normed."""
+    for c in qk_norm_of_odd_hidden():
+        for n in range(1, 17):
+            for b in (batch(n_seqs=n, n_tokens=n, max_q=1, max_ctx=20),
+                      batch(n_seqs=1, n_tokens=n, max_q=n, max_ctx=0)):
+                m = T.WorkspaceMap()
+                assert lib.tri_workspace_layout(ctypes.byref(c), ctypes.byref(b),
+                                                ctypes.byref(m)) == 0
+                plane = 4 * n * (c.n_q_heads + 2 * c.n_kv_heads) * 64
+                act_end = m.act + -(-2 * n * c.ffn_dim // 256) * 256
+                assert m.total - act_end >= plane, (c.hidden, n, m.total - act_end, plane)

@@ -57,3 +57,21 @@ def test_stream_prefill_of_few_tokens():
     rows = np.arange(7)
     x1, act, w = stage_parity(cs, ws, rows, label="stream prefill")
     check_down(cs, out, x1, act, w, rows, "stream prefill")
+
+
+@pytest.mark.parametrize("hidden,heads,n", [(192, 3, 1), (192, 3, 16), (960, 15, 16), (64, 1, 17)])
+def test_stream_qk_norm_of_odd_hidden_stays_in_its_workspace(hidden, heads, n):
+    """K not cut (hidden an odd multiple of 64): the normed q/k/v's fp32 plane,
+    in a workspace of exactly its size with a pattern behind it."""
+    import torch
+    cfg = LayerConfig(hidden=hidden, n_q_heads=heads, n_kv_heads=heads, head_dim=64, ffn_dim=320,
+                      qk_norm=True)
+    cs = Case(cfg, B(list(range(n)), [3 * i % 20 for i in range(n)], [1] * n), n, 64, seed=43)
+    need = T.workspace_size(cs.dl.cfg, cs.db)
+    buf = torch.full((need + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    out, ws = T.layer_decode(cs.dl.cfg, cs.dl.w, cs.cache, cs.db, cs.x, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0xA5).all())
+    rows = np.arange(n)
+    x1, act, w = stage_parity(cs, ws, rows, label=f"stream qk-norm {hidden} n={n}")
+    check_down(cs, out, x1, act, w, rows, f"stream qk-norm {hidden} n={n}")
