@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan.hpp"
+
 namespace tri {
 
 typedef __bf16 bf16;
@@ -77,9 +79,6 @@ __device__ __forceinline__ float group16_sum(float v) {
 __device__ __forceinline__ float silu(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
-
-__host__ __device__ constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 
 // ---- operand tiles in LDS (GEMMs): rows of 64 bf16.
 // LDS has 64 banks of 4 bytes (a 256-byte window).  A tile row is 128 bytes,

@@ -189,9 +189,10 @@ __device__ __forceinline__ int b_row_of(int kind, int tn, int nt, int ffn) {
 // conflicts).  Piece j of wave w in a half tile covers its rows 2 L and 2 L + 1,
 // L = w + 8 j; lane l writes position l % 32 of row 2 L + l / 32, so it fetches
 // logical chunk (l % 32) ^ ((2 w + l / 32) % 16) (the swizzle is an
-// involution).  Rows past M read as zero through the descriptor's range.
+// involution).  Rows past M, and columns past the end of row M - 1, read as zero
+// through the descriptor's range.
 struct ResPf {
-  __amdgpu_buffer_rsrc_t rsrc;  // residual of the tile's rows (rows past M out of range)
+  __amdgpu_buffer_rsrc_t rsrc;  // residual of the tile's rows (resid_range_bytes)
   uint32_t voff;                // lane part: row l / 32 of the piece, source chunk
   int ld_bytes;                 // residual row stride in bytes
   bool on;
@@ -1247,7 +1248,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
     const int ld_bytes = epi.ldr * 2;
     rp = ResPf{__builtin_amdgcn_make_buffer_rsrc(
                    (void*)((const bf16*)epi.resid + (int64_t)tm * BM * epi.ldr + tn * BN),
-                   (short)0, (int)((int64_t)(M - tm * BM) * ld_bytes), 0x00020000),
+                   (short)0, resid_range_bytes(M, epi.ldr, tm * BM, tn * BN, BM), 0x00020000),
                (uint32_t)((lane >> 5) * ld_bytes +
                           (((lane & 31) ^ ((2 * wv + (lane >> 5)) & 15)) << 4)),
                ld_bytes, u < 0 && K / kBK >= 2};

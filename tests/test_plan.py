@@ -1,0 +1,41 @@
+"""The launch arithmetic of csrc/plan.hpp, compiled for the host (no GPU, no HIP)."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2606_29629_amd", "csrc")
+WRAP = """
+#include "plan.hpp"
+extern "C" int resid_range(int M, int ld, int row0, int col0, int rows) {
+  return tri::resid_range_bytes(M, ld, row0, col0, rows);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("clang++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "wrap.cpp").write_text(WRAP)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC,
+                    str(d / "wrap.cpp"), "-o", str(d / "wrap.so")], check=True)
+    return ctypes.CDLL(str(d / "wrap.so"))
+
+
+@pytest.mark.parametrize("N", [64, 256, 896, 3584, 4100])
+@pytest.mark.parametrize("M", [1, 255, 256, 257, 1061, 16384])
+def test_residual_prefetch_stays_inside_the_residual(plan, M, N):
+    """A 256 x 256 tile's descriptor covers the tile's valid elements and ends
+    no later than the tensor (N not a multiple of 256: the last column tile)."""
+    for row0 in {0, (M - 1) // 256 * 256}:
+        for col0 in range(0, N, 256):
+            end = plan.resid_range(M, N, row0, col0, 256)
+            rows, cols = min(256, M - row0), min(256, N - col0)
+            assert end >= ((rows - 1) * N + cols) * 2
+            assert (row0 * N + col0) * 2 + end <= M * N * 2
