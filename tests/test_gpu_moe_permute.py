@@ -1,7 +1,6 @@
 """The routed order of a step (workspace `perm`): pairs grouped by expert,
 ascending within one, at the limits of the one-workgroup permutation (1024
-pairs) and of the expert count, and top-k routes against the reference order
-of the library's own logits (ties to the lower expert: duplicated router rows).
+pairs) and of the expert count; and the top-k of logits with ties, -inf and NaN.
 """
 import numpy as np
 import pytest
@@ -41,3 +40,31 @@ def test_permutation_groups_pairs_by_expert(E, k, n):
     if E > 64:  # the duplicated expert: never ahead of its lower twin
         for row in idx.tolist():
             assert E - 1 not in row or (0 in row and row.index(0) < row.index(E - 1))
+
+
+@pytest.mark.parametrize("E,k,finite", [(8, 5, 2), (70, 16, 4), (256, 3, 1), (8, 8, 0)])
+def test_topk_of_infinite_logits(E, k, finite):
+    """Distinct experts, in descending order with ties to the lower index, also
+    where fewer than k logits are above -inf; NaN logits come last."""
+    import torch
+    cfg = LayerConfig(hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=64, n_experts=E, top_k=k,
+                      expert_ffn_dim=64)
+    h = torch.zeros(3, 256, device="cuda")
+    h[:, 0] = 1.0  # the logits are the router's first column
+    col = torch.full((E,), -float("inf"))
+    chosen = [(5 * i + 3) % E for i in range(finite)]
+    col[chosen] = torch.arange(finite, 0, -1).float()
+    for nan in (False, True):
+        wr = torch.zeros(E, 256, dtype=torch.bfloat16, device="cuda")
+        if nan:
+            col[E - 1] = float("nan")
+        wr[:, 0] = col.to(torch.bfloat16).cuda()
+        idx = torch.empty(3, k, dtype=torch.int32, device="cuda")
+        w = torch.empty(3, k, dtype=torch.float32, device="cuda")
+        T.moe_route(T.make_config(cfg), h, wr, idx, w)
+        torch.cuda.synchronize()
+        rest = [e for e in range(E) if e not in chosen and not (nan and e == E - 1)]
+        want = (chosen + rest + [E - 1] * nan)[:k]
+        assert idx.tolist() == [want] * 3
+        if finite and not nan:
+            assert torch.all(w[:, finite:] == 0) and torch.allclose(w.sum(1).cpu(), torch.ones(3))
