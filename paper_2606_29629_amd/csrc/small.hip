@@ -304,11 +304,22 @@ __global__ __launch_bounds__(256) void split3_kernel(Split3Jobs jobs) {
 }
 
 hipError_t launch_split3(const Split3Jobs& jobs, hipStream_t s) {
-  int64_t n = 0;
-  for (int k = 0; k < jobs.n; ++k) n += jobs.job[k].rows * (jobs.job[k].cols / 4);
-  if (n == 0) return hipSuccess;
-  split3_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(jobs);
-  return hipGetLastError();
+  int64_t threads[kMaxSplit3];
+  for (int k = 0; k < jobs.n; ++k) threads[k] = jobs.job[k].rows * (jobs.job[k].cols / 4);
+  for (int k = 0; k < jobs.n;) {
+    const int end = jobs_of_launch(threads, k, jobs.n);
+    Split3Jobs part{};
+    int64_t n = 0;
+    for (; k < end; ++k) {
+      part.job[part.n++] = jobs.job[k];
+      n += threads[k];
+    }
+    if (n == 0) continue;
+    split3_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace tri

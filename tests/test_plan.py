@@ -13,6 +13,9 @@ WRAP = """
 extern "C" int resid_range(int M, int ld, int row0, int col0, int rows) {
   return tri::resid_range_bytes(M, ld, row0, col0, rows);
 }
+extern "C" int jobs_of_launch(const int64_t* threads, int first, int n) {
+  return tri::jobs_of_launch(threads, first, n);
+}
 """
 
 
@@ -39,3 +42,24 @@ def test_residual_prefetch_stays_inside_the_residual(plan, M, N):
             rows, cols = min(256, M - row0), min(256, N - col0)
             assert end >= ((rows - 1) * N + cols) * 2
             assert (row0 * N + col0) * 2 + end <= M * N * 2
+
+
+@pytest.mark.parametrize("threads", [
+    [1, 2, 3, 4],
+    [2 ** 20, 2 ** 20, 2 ** 30, 2 ** 29],                  # a 7B layer's weights and more: one launch
+    [2 ** 22, 2 ** 22, 3 * 2 ** 30, 3 * 2 ** 29],           # 256 experts of 3072 x 8192: two
+    [2 ** 31, 2 ** 31, 2 ** 31, 2 ** 31],                   # each fits, no two do
+    [2 ** 32 - 256, 1, 1, 1], [1, 1, 1, 2 ** 32 - 256], [2 ** 33, 1, 1, 1],
+])
+def test_jobs_of_a_launch_stay_under_the_grid_limit(plan, threads):
+    """Every job is launched once, none together with others past 2^32 threads
+    (what a launch per job takes is taken together as well)."""
+    arr = (ctypes.c_int64 * 4)(*threads)
+    first, launches = 0, 0
+    while first < 4:
+        end = plan.jobs_of_launch(arr, first, 4)
+        assert first < end <= 4
+        blocks = -(-sum(threads[first:end]) // 256)
+        assert end == first + 1 or blocks * 256 < 2 ** 32
+        first, launches = end, launches + 1
+    assert launches == 1 or sum(threads) > 2 ** 32 - 256
