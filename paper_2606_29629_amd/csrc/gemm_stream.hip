@@ -168,13 +168,14 @@ __global__ __launch_bounds__(W * 64) void stream_gemm_kernel(const bf16* __restr
     a_off[j] = r < M ? (uint32_t)(((int64_t)r * lda + swz(r, lane & 7) * 8) * 2) : 0x80000000u;
   }
   // The wave's i-th k-tile of a block is wv + W i.  The stream runs D tiles
-  // ahead; past the last block its loads are out of range (zeros, no
-  // traffic), which keeps the load count uniform.
+  // ahead; past the last block, and in a wave with no k-tile at all (fewer
+  // k-tiles than waves), its loads are out of range (zeros, no traffic), which
+  // keeps the load count uniform.
   const int KT = K / kSBK;
   const int nt = wv < KT ? (KT - wv + W - 1) / W : 0;
   int ib = blockIdx.x, ii = 0, islot = 0;  // the next tile to load
   auto issue = [&]() {
-    const uint32_t kill = ib < n_blk ? 0u : 0x80000000u;
+    const uint32_t kill = ib < n_blk && nt > 0 ? 0u : 0x80000000u;
     const int kb = (wv + W * ii) * kSBK * 2;
     bf16* dst = ring + islot * TILE;
 #pragma unroll
