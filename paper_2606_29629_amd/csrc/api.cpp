@@ -102,20 +102,20 @@ size_t part_bytes(const tri_layer_config* c, const tri_batch* b) {
   size_t p = flash_part_bytes(c, b) +
              attn_decode_partial_bytes(b->n_seqs, c->n_q_heads, D, b->max_ctx_len + 1);
   if (T > 0) {
-    // Skinny-path partials.  Weight streams (16 rows), 64-row and 128-row batches
-    // need different planes, so a batch reserves them for the largest batch of
-    // each kind up to its own size: the size never shrinks as n_tokens grows.
+    // Skinny-path partials.  Weight streams, 64-row and 128-row batches need
+    // different planes, so a batch reserves them for the largest batch of each
+    // kind up to its own size: the size never shrinks as n_tokens grows.
     auto mx = [](size_t a, size_t b2) { return a > b2 ? a : b2; };
-    auto skinny = [&](int Ts) {
-      size_t g = skinny_partial_bytes(Ts, Nqkv, H, EPI_QKV, (c->flags & TRI_F_QK_NORM) != 0);
-      g = mx(g, skinny_partial_bytes(Ts, H, c->n_q_heads * D, EPI_RESID));
-      if (!is_moe(c)) {
-        g = mx(g, skinny_partial_bytes(Ts, 2 * c->ffn_dim, H, EPI_SWIGLU));
-        g = mx(g, skinny_partial_bytes(Ts, H, c->ffn_dim, EPI_RESID));
-      }
-      return g;
+    auto skinny = [&](int N, int K, int kind, bool paired, bool qk_norm = false) {
+      for (const int most : {stream_rows(N, K, paired), 64, kSkinnyMaxRows})
+        p = mx(p, skinny_partial_bytes(std::min(T, most), N, K, kind, qk_norm));
     };
-    for (const int most : {kStreamMaxRows, 64, kSkinnyMaxRows}) p = mx(p, skinny(std::min(T, most)));
+    skinny(Nqkv, H, EPI_QKV, true, (c->flags & TRI_F_QK_NORM) != 0);
+    skinny(H, c->n_q_heads * D, EPI_RESID, false);
+    if (!is_moe(c)) {
+      skinny(2 * c->ffn_dim, H, EPI_SWIGLU, true);
+      skinny(H, c->ffn_dim, EPI_RESID, false);
+    }
     // Large-M GEMMs: fp32 partials of their tail tiles (a constant bound, so
     // the size stays non-decreasing in n_tokens).
     if (T > kSkinnyMaxRows) p = mx(p, gemm_tail_bytes());

@@ -1984,8 +1984,8 @@ __global__ __launch_bounds__(kNormRowThreads) void splitk_resid_norm_kernel(
   }
 }
 
-// Decode projections (17 .. 128 rows; fewer run as weight streams,
-// launch_stream).  The arithmetic intensity is ~M flop
+// Decode projections of up to 128 rows that do not run as weight streams
+// (stream_rows).  The arithmetic intensity is ~M flop
 // per weight byte, so the weight stream from HBM sets the time: skinny
 // 64 x 64 tiles (two or four waves) give ~600 workgroups on the large
 // projections -- every one resident at once, each a short run of weight rows,
@@ -2032,15 +2032,18 @@ static hipError_t run_skinny_planes(const void* A, int lda, const void* B, int l
   return run_gemm<64, kSkinnyBN, 2, 1, EPI_STORE_F32>(A, lda, B, ldb, M, N, K, pe, s, splits);
 }
 
-// Whether the projection runs as one fp32 plane finished by splitk_epi_kernel:
-// the q/k norm of a stream's few rows, which needs whole heads.
-static bool stream_norm_plane(int M, int kind, bool qk_norm) {
-  return M <= kStreamMaxRows && kind == EPI_QKV && qk_norm;
+// Whether the projection runs as a weight stream, and if so as one fp32 plane
+// finished by splitk_epi_kernel: the q/k norm, which needs whole heads.
+static bool streams(int M, int N, int K, int kind) {
+  return M <= stream_rows(N, K, kind == EPI_SWIGLU || kind == EPI_QKV);
+}
+static bool stream_norm_plane(int M, int N, int K, int kind, bool qk_norm) {
+  return kind == EPI_QKV && qk_norm && streams(M, N, K, kind);
 }
 
 size_t skinny_partial_bytes(int M, int N, int K, int kind, bool qk_norm) {
   const int s = skinny_splits(M, N, K, kind);
-  return s > 1 || stream_norm_plane(M, kind, qk_norm) ? (size_t)s * M * N * sizeof(float) : 0;
+  return s > 1 || stream_norm_plane(M, N, K, kind, qk_norm) ? (size_t)s * M * N * sizeof(float) : 0;
 }
 
 template <int BM, int WGM>
@@ -2078,8 +2081,8 @@ static hipError_t run_stream_plane(const void* A, int lda, const void* B, int ld
 hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                          const Epi& epi, float* part, hipStream_t s) {
   if (M == 0) return hipSuccess;
-  if (M <= kStreamMaxRows) {
-    if (!stream_norm_plane(M, epi.kind, epi.q_norm != nullptr))
+  if (streams(M, N, K, epi.kind)) {
+    if (!stream_norm_plane(M, N, K, epi.kind, epi.q_norm != nullptr))
       return launch_stream(A, lda, B, ldb, M, N, K, epi, s);
     hipError_t e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
     if (e != hipSuccess) return e;
@@ -2104,7 +2107,7 @@ hipError_t launch_skinny_resid_norm(const void* A, int lda, const void* B, int l
   if (M == 0) return hipSuccess;
   int splits = 1;
   hipError_t e;
-  if (M <= kStreamMaxRows) {
+  if (streams(M, N, K, EPI_RESID)) {
     e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
   } else {
     splits = skinny_splits(M, N, K, EPI_RESID);

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan.hpp"
+
 namespace tri {
 
 struct BatchDev {
@@ -130,8 +132,9 @@ int gemm_planes_splits(int M, int N, int K);
 hipError_t launch_gemm_planes(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                               float* planes, int splits, hipStream_t s);
 
-// Decode projections (M <= 128): skinny tiles, split-K for narrow N; fp32
-// partials in `part` (skinny_partial_bytes) reduced by an epilogue kernel.
+// Decode projections (M <= 128): weight streams up to stream_rows() rows, else
+// skinny tiles, split-K for narrow N; fp32 partials in `part`
+// (skinny_partial_bytes) reduced by an epilogue kernel.
 int skinny_splits(int M, int N, int K, int kind);
 // The O projection of a short batch fused with its residual add and the
 // following RMSNorm (split-K planes reduced row by row): used when this
@@ -146,7 +149,6 @@ hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, 
 
 // Projections of at most kStreamMaxRows rows as weight streams, the epilogue
 // fused (EPI_QKV without the q/k norm).
-constexpr int kStreamMaxRows = 16;
 hipError_t launch_stream(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                          const Epi& epi, hipStream_t s);
 // gate/up (EPI_SWIGLU) on RMSNorm(x), which is written to nrm.h: for the few

@@ -1,7 +1,8 @@
 """Short-batch projections as weight streams (at most 16 tokens), at the sizes
 where they can go wrong: fewer k-tiles than waves, one row, 8 / 9 and 16 / 17
 tokens (the limits of the forms), a last block of 4 weight rows, more blocks
-than resident workgroups.  tri_linear against the oracle's projection, and
+than resident workgroups, and the rows at which a narrow matrix with a long K takes
+the skinny tiles instead.  tri_linear against the oracle's projection, and
 every stage of a layer step (q/k/v, O, gate/up with its own RMSNorm, down) on
 identical inputs; tolerances as in test_gpu_layer.py (1 bf16 ulp).
 """
@@ -19,7 +20,7 @@ from test_gpu_layer import B, Case, assert_rounded, check_down, stage_parity
 pytestmark = pytest.mark.gpu
 
 LINEAR = [(1, 4, 64), (3, 36, 128), (8, 516, 448), (9, 260, 576), (16, 1000, 4096),
-          (2, 20004, 320), (13, 24580, 192)]
+          (2, 20004, 320), (13, 24580, 192), (2, 516, 8192), (3, 516, 8192), (16, 260, 12288)]
 
 
 @pytest.mark.parametrize("M,N,K", LINEAR)
@@ -34,11 +35,12 @@ def test_stream_linear(M, N, K):
 
 
 D128 = LayerConfig(hidden=512, n_q_heads=5, n_kv_heads=1, head_dim=128, ffn_dim=1088, qkv_bias=True)
+LONG = LayerConfig(hidden=6144, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=64, qk_norm=True)
 WIDE = LayerConfig(hidden=4096, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=192)
 
 
 @pytest.mark.parametrize("cfg,n", [(layer_c1(), 1), (layer_c1(), 9), (D128, 3), (D128, 8), (D128, 16),
-                                   (D128, 17), (WIDE, 4), (WIDE, 5),
+                                   (D128, 17), (WIDE, 4), (WIDE, 5), (LONG, 2), (LONG, 3),
                                    (dataclasses.replace(layer_talker(), qkv_bias=True), 1),
                                    (dataclasses.replace(D128, qk_norm=True), 7)])
 def test_stream_layer_stages(cfg, n):

@@ -16,6 +16,7 @@ extern "C" int resid_range(int M, int ld, int row0, int col0, int rows) {
 extern "C" int jobs_of_launch(const int64_t* threads, int first, int n) {
   return tri::jobs_of_launch(threads, first, n);
 }
+extern "C" int stream_rows(int N, int K, int paired) { return tri::stream_rows(N, K, paired != 0); }
 """
 
 
@@ -46,9 +47,9 @@ def test_residual_prefetch_stays_inside_the_residual(plan, M, N):
 
 @pytest.mark.parametrize("threads", [
     [1, 2, 3, 4],
-    [2 ** 20, 2 ** 20, 2 ** 30, 2 ** 29],                  # a 7B layer's weights and more: one launch
-    [2 ** 22, 2 ** 22, 3 * 2 ** 30, 3 * 2 ** 29],           # 256 experts of 3072 x 8192: two
-    [2 ** 31, 2 ** 31, 2 ** 31, 2 ** 31],                   # each fits, no two do
+    [2 ** 20, 2 ** 20, 2 ** 30, 2 ** 29],          # one launch
+    [2 ** 22, 2 ** 22, 3 * 2 ** 30, 3 * 2 ** 29],  # 256 experts of 3072 x 8192: two
+    [2 ** 31, 2 ** 31, 2 ** 31, 2 ** 31],          # each fits, no two do
     [2 ** 32 - 256, 1, 1, 1], [1, 1, 1, 2 ** 32 - 256], [2 ** 33, 1, 1, 1],
 ])
 def test_jobs_of_a_launch_stay_under_the_grid_limit(plan, threads):
@@ -63,3 +64,19 @@ def test_jobs_of_a_launch_stay_under_the_grid_limit(plan, threads):
         assert end == first + 1 or blocks * 256 < 2 ** 32
         first, launches = end, launches + 1
     assert launches == 1 or sum(threads) > 2 ** 32 - 256
+
+
+@pytest.mark.parametrize("rows,N,K,paired,stream", [
+    # narrow with a long K: the streams took 1.1 to 1.8 times the skinny tiles' time
+    (5, 1024, 16384, False, False), (16, 256, 16384, False, False), (16, 1024, 8192, False, False),
+    (16, 2048, 8192, False, False), (16, 3584, 18944, False, False), (8, 1024, 8192, True, False),
+    (9, 1024, 6144, True, False), (1, 1024, 8192, True, False), (12, 1024, 6144, False, False),
+    # the rest: down to 0.7 of it
+    (12, 3584, 18944, False, True), (16, 3584, 3584, False, True), (16, 896, 4864, False, True),
+    (16, 2048, 4096, False, True), (2, 1024, 8192, False, True), (16, 8192, 8192, False, True),
+    (16, 37888, 3584, True, True), (16, 4608, 3584, True, True), (16, 1152, 896, True, True),
+    (16, 5120, 2048, True, True), (16, 768, 4096, True, True), (16, 4, 64, False, True),
+])
+def test_streams_where_they_measured_faster(plan, rows, N, K, paired, stream):
+    assert (rows <= plan.stream_rows(N, K, paired)) == stream
+    assert 0 <= plan.stream_rows(N, K, paired) <= 16
