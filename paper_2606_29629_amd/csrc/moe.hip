@@ -54,40 +54,32 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
 __device__ __forceinline__ void route_topk(const float (&vin)[4], int E, int k, int renorm,
                                            int lane, int32_t* __restrict__ idx,
                                            float* __restrict__ w) {
+  // A chosen expert's logit becomes NaN, which no maximum is and which equals
+  // none (-inf would come again where fewer than k logits lie above it).
   float v[4];
-  unsigned open = 0;  // bit q: expert lane + 64 q exists and is not chosen yet
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    v[q] = vin[q];
-    open |= lane + 64 * q < E ? 1u << q : 0u;
-  }
+  for (int q = 0; q < 4; ++q) v[q] = lane + 64 * q < E ? vin[q] : NAN;
   float my_v = -INFINITY;
   int my_i = 0;
   for (int s = 0; s < k; ++s) {
     // the wave's highest logit, then the lowest expert holding it (experts of a
-    // smaller q come first, then those of a lower lane); -inf is a logit like
-    // any other, NaN comes after all of them
-    const float bv = wave_max_dpp(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    // smaller q come first, then those of a lower lane)
+    float bv = wave_max_dpp(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
     int bi = -1;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const unsigned long long eq = __builtin_amdgcn_ballot_w64(v[q] == bv && (open >> q & 1));
+      const unsigned long long eq = __builtin_amdgcn_ballot_w64(v[q] == bv);
       if (bi < 0 && eq) bi = 64 * q + __builtin_ctzll(eq);
     }
-    if (bi < 0) {  // only NaNs are left: the lowest expert (k <= E: there is one)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const unsigned long long left = __builtin_amdgcn_ballot_w64(open >> q & 1);
-        if (bi < 0 && left) bi = 64 * q + __builtin_ctzll(left);
-      }
+    if (bi < 0) {  // only NaN logits are left: the lowest expert not chosen yet (k <= E)
+      do ++bi;
+      while (__builtin_amdgcn_ballot_w64(lane < s && my_i == bi));
+      bv = -INFINITY;
     }
     if (lane == s) { my_v = bv; my_i = bi; }
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (lane + 64 * q == bi) {
-        v[q] = -INFINITY;
-        open &= ~(1u << q);
-      }
+      if (lane + 64 * q == bi) v[q] = NAN;
   }
   const float m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
                                                 __builtin_bit_cast(int, my_v)));
