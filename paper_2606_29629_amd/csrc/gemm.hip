@@ -2005,7 +2005,7 @@ constexpr int kSkinnyBN = 64;
 
 static int skinny_bm(int M) { return M <= 64 ? 64 : 128; }
 
-int skinny_splits(int M, int N, int K, int kind) {
+static int skinny_splits(int M, int N, int K, int kind) {
   const int tiles = cdiv(M, skinny_bm(M)) * cdiv(N, kSkinnyBN);
   const int target = M > 64 ? 100 : 200;
   int s = 1;
@@ -2032,18 +2032,22 @@ static hipError_t run_skinny_planes(const void* A, int lda, const void* B, int l
   return run_gemm<64, kSkinnyBN, 2, 1, EPI_STORE_F32>(A, lda, B, ldb, M, N, K, pe, s, splits);
 }
 
-// Whether the projection runs as a weight stream, and if so as one fp32 plane
-// finished by splitk_epi_kernel: the q/k norm, which needs whole heads.
 static bool streams(int M, int N, int K, int kind) {
   return M <= stream_rows(N, K, kind == EPI_SWIGLU || kind == EPI_QKV);
 }
-static bool stream_norm_plane(int M, int N, int K, int kind, bool qk_norm) {
-  return kind == EPI_QKV && qk_norm && streams(M, N, K, kind);
+
+// fp32 planes [planes][M][N] that a short projection leaves in `part` for a
+// second kernel, 0 if its own epilogue finishes it.  norm: that kernel also
+// normalises (the q/k norm, RMSNorm after a residual), which needs whole heads
+// or rows; a stream needs a plane for nothing else.
+static int skinny_planes(int M, int N, int K, int kind, bool norm) {
+  if (streams(M, N, K, kind)) return norm ? 1 : 0;
+  const int s = skinny_splits(M, N, K, kind);
+  return s > 1 ? s : 0;
 }
 
-size_t skinny_partial_bytes(int M, int N, int K, int kind, bool qk_norm) {
-  const int s = skinny_splits(M, N, K, kind);
-  return s > 1 || stream_norm_plane(M, N, K, kind, qk_norm) ? (size_t)s * M * N * sizeof(float) : 0;
+size_t skinny_partial_bytes(int M, int N, int K, int kind, bool norm) {
+  return (size_t)skinny_planes(M, N, K, kind, norm) * M * N * sizeof(float);
 }
 
 template <int BM, int WGM>
@@ -2081,40 +2085,37 @@ static hipError_t run_stream_plane(const void* A, int lda, const void* B, int ld
 hipError_t launch_skinny(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                          const Epi& epi, float* part, hipStream_t s) {
   if (M == 0) return hipSuccess;
+  const int planes = skinny_planes(M, N, K, epi.kind, epi.kind == EPI_QKV && epi.q_norm);
   if (streams(M, N, K, epi.kind)) {
-    if (!stream_norm_plane(M, N, K, epi.kind, epi.q_norm != nullptr))
-      return launch_stream(A, lda, B, ldb, M, N, K, epi, s);
+    if (planes == 0) return launch_stream(A, lda, B, ldb, M, N, K, epi, s);
     hipError_t e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
     if (e != hipSuccess) return e;
     const int64_t n = (int64_t)M * (epi.n_q_heads + 2 * epi.n_kv_heads) * (epi.head_dim / 2);
     splitk_epi_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(part, 1, M, N, epi);
     return hipGetLastError();
   }
-  const int splits = skinny_splits(M, N, K, epi.kind);
-  if (splits == 1 && epi.kind == EPI_QKV) return launch_gemm(A, lda, B, ldb, M, N, K, epi, nullptr, s);
+  if (planes == 0 && epi.kind == EPI_QKV)
+    return launch_gemm(A, lda, B, ldb, M, N, K, epi, nullptr, s);
+  const int splits = planes > 0 ? planes : 1;
   if (M <= 64) return run_skinny<64, 2>(A, lda, B, ldb, M, N, K, epi, part, splits, s);
   return run_skinny<128, 4>(A, lda, B, ldb, M, N, K, epi, part, splits, s);
 }
 
 bool skinny_resid_norm_fused(int M, int N, int K) {
   return M <= 128 && M > 0 && N % 4 == 0 && N <= kNormRowThreads * 4 * kNormRowChunks &&
-         skinny_splits(M, N, K, EPI_RESID) > 1;
+         skinny_planes(M, N, K, EPI_RESID, true) > 0;
 }
 
 hipError_t launch_skinny_resid_norm(const void* A, int lda, const void* B, int ldb, int M, int N,
                                     int K, const void* resid, int ldr, void* out, int ldo,
                                     const void* g, void* y, float eps, float* part, hipStream_t s) {
   if (M == 0) return hipSuccess;
-  int splits = 1;
-  hipError_t e;
-  if (streams(M, N, K, EPI_RESID)) {
-    e = run_stream_plane(A, lda, B, ldb, M, N, K, part, s);
-  } else {
-    splits = skinny_splits(M, N, K, EPI_RESID);
-    e = run_skinny_planes(A, lda, B, ldb, M, N, K, part, splits, EPI_RESID, s);
-  }
+  const int planes = skinny_planes(M, N, K, EPI_RESID, true);
+  const hipError_t e = streams(M, N, K, EPI_RESID)
+                           ? run_stream_plane(A, lda, B, ldb, M, N, K, part, s)
+                           : run_skinny_planes(A, lda, B, ldb, M, N, K, part, planes, EPI_RESID, s);
   if (e != hipSuccess) return e;
-  splitk_resid_norm_kernel<<<M, kNormRowThreads, 0, s>>>(part, splits, M, N, (const bf16*)resid,
+  splitk_resid_norm_kernel<<<M, kNormRowThreads, 0, s>>>(part, planes, M, N, (const bf16*)resid,
                                                         ldr, (bf16*)out, ldo, (const bf16*)g,
                                                         (bf16*)y, eps);
   return hipGetLastError();

@@ -335,6 +335,9 @@ def test_linear_validation(lib):
     big = ctypes.c_size_t()
     assert lib.tri_linear_workspace_size(1024, 4096, 4096, ctypes.byref(big)) == 0
     assert big.value == 256 * 256 * 256 * 4   # the large GEMMs' tail tiles
+    few = ctypes.c_size_t(1)
+    assert lib.tri_linear_workspace_size(16, 4096, 4096, ctypes.byref(few)) == 0
+    assert few.value == 0                     # a weight stream: no partials
     assert lib.tri_linear_workspace_size(8, 64, 100, ctypes.byref(ws)) == T.TRI_ERR_SHAPE
     assert lib.tri_linear_workspace_size(8, 6, 64, ctypes.byref(ws)) == T.TRI_ERR_SHAPE
     assert lib.tri_linear_workspace_size(0, 64, 64, ctypes.byref(ws)) == T.TRI_ERR_SHAPE
@@ -388,8 +391,9 @@ def test_workspace_size_never_shrinks_as_tokens_grow(lib):
               n_experts=128, top_k=8, expert_ffn_dim=768, flags=T.TRI_F_MOE)
     shapes = (lambda n: batch(n_seqs=n, n_tokens=n, max_q=1, max_ctx=4096),  # decode steps
               lambda n: batch(n_seqs=1, n_tokens=n, max_q=n, max_ctx=0))     # one prompt
-    odd = qk_norm_of_odd_hidden()[2]
-    for c in (dense, moe, odd):
+    narrow = cfg(hidden=8192, n_q_heads=4, n_kv_heads=1, head_dim=128, ffn_dim=512,
+                 flags=T.TRI_F_QK_NORM)  # streams up to a few rows only
+    for c in (dense, moe, narrow, *qk_norm_of_odd_hidden()):
         for shape in shapes:
             prev = 0
             for n in list(range(1, 300)) + [512, 1024, 4096]:
