@@ -4,9 +4,89 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace tri {
 
+constexpr int kBK = 64;  // k per GEMM k-tile
+
 constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// Tiles of the final partial round: total % CUs, or all of them when the
+// GEMM has fewer tiles than CUs.
+constexpr int tail_tiles(int total, int G) {
+  return total > G ? total % G : (total == G ? 0 : total);
+}
+
+constexpr int kMaxTailSplit = 8;  // K-parts of a tail tile, at most
+
+// How a GEMM of M x N x K runs: on 256 x 256 tiles, the last partial round of
+// them whole (split 1), in `split` K-parts, or as 128-row halves (split 0), or
+// on 128 x 256 tiles, or on 128 x 128 tiles, all of them split in K where they
+// would fill less than half of the CUs.  The choice is
+// the least of the forms' estimated times: rounds of workgroups (one per CU)
+// of KT k-tiles, plus per round the fill and the epilogue, plus for a K-split
+// the partials written and read back and one more launch.  The constants are
+// measured at clocks the small GEMMs hold (per k-tile: 256 x 256 1.05 us, 128 x
+// 256 0.74 us, 128 x 128 0.60 us; they are bound by LDS, 256, 176 and 128 KB a
+// k-tile through 128 B per clock, so the largest tile does the most per CU
+// and the small ones only pay where they fill more of the CUs).
+struct GemmPlan {
+  int bm, bn, split;
+};
+constexpr float kUs256 = 1.05f, kUs128x256 = 0.74f, kUs128 = 0.60f;  // us per k-tile
+constexpr float kUsRound256 = 12.f, kUsRound128x256 = 8.f, kUsRound128 = 6.f;  // us per round
+constexpr float kUsLaunch = 5.f;         // one more launch
+constexpr float kPartialMbPerUs = 4.2f;  // fp32 partials, written or read
+
+// N: weight rows (gate and up for SwiGLU); have_tail: there is room for partials;
+// G: CUs.
+inline GemmPlan gemm_plan(int M, int N, int K, bool swiglu, bool have_tail, bool routed, int G) {
+  const int kt = K / kBK;
+  const int cols256 = cdiv(N, 256), t256 = cdiv(M, 256) * cols256;
+  GemmPlan best{256, 256, 1};
+  float cost = cdiv(t256, G) * (kt * kUs256 + kUsRound256);
+  auto offer = [&](float c, GemmPlan p) {
+    if (c < cost) {
+      cost = c;
+      best = p;
+    }
+  };
+  const int rem = tail_tiles(t256, G);
+  const float rounds = (t256 - rem) / G * (kt * kUs256 + kUsRound256);
+  // The rows of a mixture of experts go on to its router, where a near tie
+  // makes another sum order another choice of experts (measured: about one
+  // token in 2000, a tenth of the rms in its output).  There K is cut only
+  // where a last round holds less than a fifth of the chip's tiles (a quarter
+  // with a long K); whole tiles sum in the same order whatever their form.
+  if (routed && have_tail) {
+    if (rem > 0 && (t256 > G || K > 8192)) {
+      int t = std::min(G / rem, kMaxTailSplit);
+      while (t > 1 && (t - 1) * cdiv(kt, t) >= kt) --t;
+      if (t > 4 || (t == 4 && K > 4096)) return {256, 256, t};
+    }
+    have_tail = false;
+  }
+  if (rem > 0) {
+    offer(rounds + cdiv(2 * rem, G) * (kt * kUs128x256 + kUsRound128x256) +
+              (t256 > rem ? kUsLaunch : 0.f),
+          {256, 256, 0});
+    if (have_tail && !swiglu)
+      for (int t = 2; t <= kMaxTailSplit && t * rem <= G && (t - 1) * cdiv(kt, t) < kt; ++t)
+        offer(rounds + cdiv(kt, t) * kUs256 + kUsRound256 + 2 * kUsLaunch +
+                  2 * rem * t * 0.262f * M / (cdiv(M, 256) * 256) / kPartialMbPerUs,
+              {256, 256, t});
+  }
+  offer(cdiv(cdiv(M, 128) * cols256, G) * (kt * kUs128x256 + kUsRound128x256), {128, 256, 1});
+  const int t128 = cdiv(M, 128) * cdiv(N, 128);
+  offer(cdiv(t128, G) * (kt * kUs128 + kUsRound128), {128, 128, 1});
+  if (have_tail && !swiglu)
+    for (int t = 2; t <= kMaxTailSplit && t * t128 <= G && (t - 1) * cdiv(kt, t) < kt; ++t)
+      offer(cdiv(kt, t) * kUs128 + kUsRound128 + 2 * kUsLaunch +
+                2 * t128 * t * 0.0655f * M / (cdiv(M, 128) * 128) / kPartialMbPerUs,
+            {128, 128, t});
+  return best;
+}
 
 // Bytes of a residual [M, ld] (bf16) that a tile of `rows` rows at (row0, col0)
 // may read, counted from its first element: its valid rows, and in the last of

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_gemm_tiles import CASES
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                     "paper_2606_29629_amd", "csrc")
 WRAP = """
@@ -17,6 +19,10 @@ extern "C" int jobs_of_launch(const int64_t* threads, int first, int n) {
   return tri::jobs_of_launch(threads, first, n);
 }
 extern "C" int stream_rows(int N, int K, int paired) { return tri::stream_rows(N, K, paired != 0); }
+extern "C" void gemm_plan(int M, int N, int K, int swiglu, int tail, int routed, int* out) {
+  const tri::GemmPlan p = tri::gemm_plan(M, N, K, swiglu != 0, tail != 0, routed != 0, 256);
+  out[0] = p.bm, out[1] = p.bn, out[2] = p.split;
+}
 """
 
 
@@ -80,3 +86,30 @@ def test_jobs_of_a_launch_stay_under_the_grid_limit(plan, threads):
 def test_streams_where_they_measured_faster(plan, rows, N, K, paired, stream):
     assert (rows <= plan.stream_rows(N, K, paired)) == stream
     assert 0 <= plan.stream_rows(N, K, paired) <= 16
+
+
+def gemm_plan(plan, M, N, K, swiglu=False, tail=True, routed=False):
+    """(rows, columns, split) of the plan on 256 CUs."""
+    out = (ctypes.c_int * 3)()
+    plan.gemm_plan(M, N, K, swiglu, tail, routed, out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("M,N,K", CASES)
+def test_gemm_edge_cases_reach_the_forms_they_name(plan, M, N, K):
+    assert gemm_plan(plan, M, N, K) == CASES[M, N, K]
+
+
+def test_k_parts_fit_the_partials(plan):
+    """A K-split's tiles times its parts never exceed the reserved round of 256
+    tiles, and no part is empty."""
+    for M in (129, 300, 544, 1061, 2817, 4115, 16384):
+        for N in (64, 516, 2048, 3584, 9216):
+            for K in (64, 448, 4096, 16384, 18944):
+                for routed in (False, True):
+                    bm, bn, split = gemm_plan(plan, M, N, K, routed=routed)
+                    if split > 1:
+                        tiles = -(-M // bm) * -(-N // bn)
+                        tail = tiles % 256 if tiles > 256 else tiles
+                        assert tail * split <= 256
+                        assert (split - 1) * -(-(K // 64) // split) < K // 64
