@@ -56,9 +56,14 @@ inline GemmPlan gemm_plan(int M, int N, int K, bool swiglu, bool have_tail, bool
   const float rounds = (t256 - rem) / G * (kt * kUs256 + kUsRound256);
   // The rows of a mixture of experts go on to its router, where a near tie
   // makes another sum order another choice of experts (measured: about one
-  // token in 2000, a tenth of the rms in its output).  There K is cut only
-  // where a last round holds less than a fifth of the chip's tiles (a quarter
-  // with a long K); whole tiles sum in the same order whatever their form.
+  // token in 2000, a tenth of the rms in its output).  Whole tiles sum in one
+  // order whatever their form, so K is not cut for the estimate's small gains,
+  // only where a last round after whole ones (or alone, with a K past 8192) is
+  // so empty that the cut pays.  Cut against whole, us (rows, in t parts): 8192 x
+  // 8192 4200 t = 8 433 / 507, 4500 t = 4 469 / 502; 10240 x 8192 3400 t = 5 446 /
+  // 488; 18432 x 4096 4500 t = 8 540 / 564, 5500 t = 5 649 / 659; 4096 x 16384 300 t =
+  // 8 79 / 116, 900 t = 4 131 / 129; at a K of 2048 it is even: 5120 x 2048 3100 t = 8
+  // 90 / 78, 3500 95 / 98, 6500 148 / 157, 3700 t = 5 107 / 100.
   if (routed && have_tail) {
     if (rem > 0 && (t256 > G || K > 8192)) {
       int t = std::min(G / rem, kMaxTailSplit);

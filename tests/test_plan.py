@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_moe_order as order
 from test_gpu_gemm_tiles import CASES
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
@@ -98,6 +99,15 @@ def gemm_plan(plan, M, N, K, swiglu=False, tail=True, routed=False):
 @pytest.mark.parametrize("M,N,K", CASES)
 def test_gemm_edge_cases_reach_the_forms_they_name(plan, M, N, K):
     assert gemm_plan(plan, M, N, K) == CASES[M, N, K]
+
+
+def test_routed_sizes_compared_bit_by_bit_differ_in_form_and_keep_k_whole(plan):
+    for n, k in order.PROJECTIONS:
+        forms = [gemm_plan(plan, m, n, k, routed=True) for m in order.SIZES]
+        assert all(split <= 1 for _, _, split in forms)
+        assert len(set(forms)) > 1
+    # (and the cut that is there: 32 of 288 tiles in the last round)
+    assert gemm_plan(plan, 2817, 6144, 2048, routed=True) == (256, 256, 8)
 
 
 def test_k_parts_fit_the_partials(plan):
