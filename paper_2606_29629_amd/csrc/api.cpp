@@ -464,7 +464,7 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
     return TRI_OK;
   }
   const int E = cfg->n_experts, k = cfg->top_k, Fe = cfg->expert_ffn_dim;
-  const int P = T * k;
+  const int P = T * k, bm = moe_tile_rows(P, E, H, Fe, cu_count());
   int32_t* idx = route_idx ? route_idx : at<int32_t>(ws, L.route_idx);
   float* rw = route_w ? route_w : at<float>(ws, L.route_w);
   int32_t* perm = at<int32_t>(ws, L.perm);
@@ -479,7 +479,7 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   }
   {
     StageTimer t_(ST_MOE_PERMUTE, s, timed);
-    TRI_HIP(launch_moe_permute(idx, P, E, moe_tile_rows(P, E), at<int32_t>(ws, L.rank),
+    TRI_HIP(launch_moe_permute(idx, P, E, bm, at<int32_t>(ws, L.rank),
                                at<int32_t>(ws, L.counts), perm, inv, seg, tile_off, s));
   }
   e = Epi{};
@@ -491,7 +491,7 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
   {
     StageTimer t_(ST_MOE_GATEUP, s, timed);
     TRI_HIP(launch_gemm_grouped(a3, 3 * H, T, perm, k, wgu3, (int64_t)2 * Fe * 3 * H, 2 * Fe,
-                                3 * H, seg, tile_off, E, P, e, s));
+                                3 * H, seg, tile_off, E, P, bm, e, s));
   }
   e = Epi{};
   e.f32 = 1;
@@ -502,7 +502,7 @@ tri_status layer_f32(const tri_layer_config* cfg, const tri_layer_weights* w,
     StageTimer t_(ST_MOE_DOWN, s, timed);
     TRI_HIP(planes(act, P, Fe, a3));
     TRI_HIP(launch_gemm_grouped(a3, 3 * Fe, P, nullptr, k, wd3, (int64_t)H * 3 * Fe, H, 3 * Fe,
-                                seg, tile_off, E, P, e, s));
+                                seg, tile_off, E, P, bm, e, s));
   }
   {
     StageTimer t_(ST_MOE_COMBINE, s, timed);
@@ -696,7 +696,7 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
 
   // ---- mixture of experts
   const int E = cfg->n_experts, k = cfg->top_k, Fe = cfg->expert_ffn_dim;
-  const int P = T * k;
+  const int P = T * k, bm = moe_tile_rows(P, E, H, Fe, cu_count());
   int32_t* idx = route_idx ? route_idx : at<int32_t>(ws, L.route_idx);
   float* rw = route_w ? route_w : at<float>(ws, L.route_w);
   int32_t* perm = at<int32_t>(ws, L.perm);
@@ -712,7 +712,7 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
   }
   {
     StageTimer t_(ST_MOE_PERMUTE, s, timed);
-    TRI_HIP(launch_moe_permute(idx, P, E, moe_tile_rows(P, E), at<int32_t>(ws, L.rank),
+    TRI_HIP(launch_moe_permute(idx, P, E, bm, at<int32_t>(ws, L.rank),
                                at<int32_t>(ws, L.counts), perm, inv, seg, tile_off, s));
   }
   e = Epi{};
@@ -723,7 +723,7 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
   {
     StageTimer t_(ST_MOE_GATEUP, s, timed);
     TRI_HIP(launch_gemm_grouped(h2, H, T, perm, k, w->w_gate_up, (int64_t)2 * Fe * H, 2 * Fe, H,
-                                seg, tile_off, E, P, e, s));
+                                seg, tile_off, E, P, bm, e, s));
   }
   e = Epi{};
   e.kind = EPI_STORE_F32;
@@ -732,7 +732,7 @@ tri_status tri::layer_call(bool decode, bool timed, const tri_layer_config* cfg,
   {
     StageTimer t_(ST_MOE_DOWN, s, timed);
     TRI_HIP(launch_gemm_grouped(act, Fe, P, nullptr, k, w->w_down, (int64_t)H * Fe, H, Fe, seg,
-                                tile_off, E, P, e, s));
+                                tile_off, E, P, bm, e, s));
   }
   {
     StageTimer t_(ST_MOE_COMBINE, s, timed);

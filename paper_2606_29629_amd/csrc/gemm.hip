@@ -1677,15 +1677,6 @@ hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, in
   }
 }
 
-// Rows per grouped-GEMM tile from the mean rows per expert: skinny tiles when
-// experts see few rows (decode), the prefill GEMM's 256 x 256 tiles when they
-// see ~224 or more (the 4 x 1024-token MoE prefill: gate/up 290 against
-// 310-360 us with 128-row tiles, down 208 against 230-245 us).
-int moe_tile_rows(int n_pairs, int n_experts) {
-  if (n_pairs <= 48 * n_experts) return 32;
-  return n_pairs >= 224 * n_experts ? 256 : 128;
-}
-
 template <int BM, int BN, int WGM, int WGN, int EK, int SH = 32>
 static hipError_t run_grouped(const void* A, int lda, int a_rows, const int32_t* perm, int top_k,
                               const void* B, int64_t b_stride, int N, int K, const int32_t* seg,
@@ -1705,9 +1696,9 @@ static hipError_t run_grouped(const void* A, int lda, int a_rows, const int32_t*
 hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t* perm, int top_k,
                                const void* B, int64_t b_stride, int N, int K, const int32_t* seg,
                                const int32_t* tile_off, int n_experts, int n_pairs,
-                               const Epi& epi, hipStream_t s) {
+                               int bm, const Epi& epi, hipStream_t s) {
   if (n_pairs == 0) return hipSuccess;
-  const int bm = moe_tile_rows(n_pairs, n_experts);
+  if (bm != 32 && bm != 128 && bm != 256) return hipErrorInvalidValue;
   const int max_tiles_m = cdiv(n_pairs, bm) + n_experts;  // each expert adds <= 1 partial tile
   if (epi.f32 && epi.kind == EPI_SWIGLU) {
     constexpr int EK = EPI_SWIGLU | kEpiF32;

@@ -198,11 +198,11 @@ hipError_t launch_attn_decode_combine(const float* part, void* out, const BatchD
 // Mixture of experts.  Grouped GEMM over experts: rows [seg[e], seg[e+1]) of
 // the routed order belong to expert e; the gate/up pass gathers A rows
 // perm[p] / top_k (perm = routed pair ids), the down pass reads A rows in
-// routed order.  Tiles of moe_tile_rows(n_pairs, n_experts) rows.
-int moe_tile_rows(int n_pairs, int n_experts);
+// routed order.  Tiles of bm rows (moe_tile_rows), as in the permutation's
+// tile_off.
 hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t* perm, int top_k,
                                const void* B, int64_t b_stride, int N, int K, const int32_t* seg,
-                               const int32_t* tile_off, int n_experts, int n_pairs,
+                               const int32_t* tile_off, int n_experts, int n_pairs, int bm,
                                const Epi& epi, hipStream_t s);
 // w_router bf16, or fp32 with w_f32 (the fp32 storage mode).
 hipError_t launch_moe_route_f32(const float* h32, const void* w_router, int T, int H, int E,

@@ -122,6 +122,29 @@ constexpr int stream_rows(int N, int K, bool paired) {
   return most < 0 ? 0 : most < kStreamMaxRows ? most : kStreamMaxRows;
 }
 
+// Rows per tile of the grouped expert GEMMs, by the mean rows per expert and by
+// whether a tile per expert and column (128 columns of ffn in gate/up, 256 of
+// hidden in down, the wider pass) is all one round of the G CUs: then 32-row
+// tiles, two workgroups per CU, last a little longer, and 128-row tiles last as
+// long as they fit in the round, counting a fifth more rows than the mean.
+//
+// Both passes at a mean of so many rows, us, for 128 experts of 768 x 2048 (E), 64 of
+// 1536 x 2048 (F), 32 of 1024 x 2048 (T), 8 of 2048 x 4096 (W):
+//   32 / 128 rows    16  E 230 / 231, F 226 / 226, T 85 / 99   24  E 248 / 240, F 254 / 231,
+//                    T 99 / 100   32  E 309 / 244, F 320 / 235, T 103 / 102   48  E 411 / 255
+//   128 / 256 rows   96  E 292 / 293, F 268 / 273   104  E 326 / 290, F 315 / 279   192  E 389
+//                    / 343, F 393 / 320, T 153 / 131
+//   in one round     W 160  130 / 142, 208  139 / 156 (256 rows leave half the CUs idle)
+inline int moe_tile_rows(int n_pairs, int n_experts, int hidden, int ffn, int G) {
+  const int64_t pairs = n_pairs, E = n_experts;
+  const int64_t cols = std::max(cdiv(ffn, 128), cdiv(hidden, 256));
+  if (pairs <= (E * cols <= G ? 24 : 20) * E) return 32;
+  if (pairs < 100 * E) return 128;
+  if (pairs >= 224 * E) return 256;
+  const int64_t tiles = (pairs * 6 / 5 + 128 * E - 1) / (128 * E);  // per expert and column
+  return E * cols * tiles <= G ? 128 : 256;
+}
+
 // A launch holds fewer than 2^32 threads per grid dimension: of the jobs
 // first .. n - 1 with `threads` threads each, the end of those that fit in one
 // launch together (at least one: a job that does not fit fails as it would alone).

@@ -238,3 +238,14 @@ def test_moe_grouped_tile_sizes(n_tok):
     exact = oracle.layer_forward(*args, rows=rows, forced_routes=gi)
     assert_e2e(to_host_f64(c.out)[rows], exact["out"], f"tiny MoE {n_tok} tokens rows",
                emul=forced["out"], strict=True)
+
+
+@pytest.mark.parametrize("experts,ffn,k,n_tok", [(8, 128, 2, 96), (8, 128, 2, 98), (64, 512, 4, 1590),
+                                                 (64, 512, 4, 1610)],
+                         ids=["last 32-row", "first 128-row", "last 128-row", "first 256-row"])
+def test_moe_grouped_tile_lines(experts, ffn, k, n_tok):
+    """At the lines between the tile forms (24 rows per expert of few experts, 100
+    of more tiles than one round)."""
+    cfg = dataclasses.replace(TINY_MOE, n_experts=experts, expert_ffn_dim=ffn, top_k=k)
+    c = MoECase(cfg, B([0, 1], [0, 5], [n_tok - 30, 30]), 2, 1664, seed=10)
+    moe_stage_parity(c, np.array([0, 1, 31, 32, n_tok - 31, n_tok - 30, n_tok - 1]))

@@ -24,6 +24,9 @@ extern "C" void gemm_plan(int M, int N, int K, int swiglu, int tail, int routed,
   const tri::GemmPlan p = tri::gemm_plan(M, N, K, swiglu != 0, tail != 0, routed != 0, 256);
   out[0] = p.bm, out[1] = p.bn, out[2] = p.split;
 }
+extern "C" int moe_tile_rows(int pairs, int experts, int hidden, int ffn) {
+  return tri::moe_tile_rows(pairs, experts, hidden, ffn, 256);
+}
 """
 
 
@@ -123,3 +126,21 @@ def test_k_parts_fit_the_partials(plan):
                         tail = tiles % 256 if tiles > 256 else tiles
                         assert tail * split <= 256
                         assert (split - 1) * -(-(K // 64) // split) < K // 64
+
+
+@pytest.mark.parametrize("mean,experts,hidden,ffn,rows", [
+    (0.25, 128, 2048, 768, 32), (20, 128, 2048, 768, 32), (21, 128, 2048, 768, 128),
+    (48, 64, 2048, 1536, 128), (99, 128, 2048, 768, 128), (100, 128, 2048, 768, 256),
+    (223, 64, 2048, 1536, 256), (256, 128, 2048, 768, 256),
+    (24, 32, 2048, 1024, 32), (25, 32, 2048, 1024, 128),
+    (160, 8, 4096, 2048, 128), (212, 8, 4096, 2048, 128), (224, 8, 4096, 2048, 256),
+    (160, 8, 4096, 3584, 256), (128, 16, 4096, 1536, 256), (250, 8, 256, 128, 256),
+])
+def test_expert_tile_rows_where_they_measured_faster(plan, mean, experts, hidden, ffn, rows):
+    assert plan.moe_tile_rows(int(mean * experts), experts, hidden, ffn) == rows
+
+
+def test_expert_tile_rows_of_the_largest_sizes(plan):
+    assert plan.moe_tile_rows(2 ** 31 - 1, 256, 8192, 2 ** 20) == 256
+    assert plan.moe_tile_rows(2 ** 31 - 1, 1, 64, 64) == 256
+    assert plan.moe_tile_rows(1, 1, 64, 64) == 32
