@@ -439,8 +439,9 @@ struct PingCols {
 // operands (1343 -> 1455 TFLOP/s), 677 -> 593 us on zeros, which draw less
 // power; gate/up at 16384 x 3584 (SwiGLU) 3380 -> 3083 us, down 1720 -> 1671 us.
 // Without the stagger of the groups 868 us; loads issued between the MFMAs
-// 840 us; s_setprio, the order of reads and loads in a phase and the order of
-// the MFMAs make no difference.
+// 840 us; a raised wave priority around the MFMAs (8 x 2048 prefill 5950 with it,
+// 5935 us without), the order of reads and loads in a phase and the order of the
+// MFMAs make no difference.
 struct PingLoop : PingCols<2> {
   static constexpr int SH = 16, BM = 256, BN = 256, NW = 8, NT = 512;
   using MF = Mfma<SH>;
@@ -535,7 +536,6 @@ struct PingLoop : PingCols<2> {
       asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
       barrier();
       if (lgkm) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -543,7 +543,6 @@ struct PingLoop : PingCols<2> {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             acc[4 * h + i][2 * g + j] = MF::mma(fb[g][j][ks], fa[i][ks], acc[4 * h + i][2 * g + j]);
-      __builtin_amdgcn_s_setprio(0);
       barrier();
     };
     using I0 = std::integral_constant<int, 0>;
@@ -701,7 +700,6 @@ struct PingSmall : PingCols<HB> {
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
       barrier();
-      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -709,7 +707,6 @@ struct PingSmall : PingCols<HB> {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             acc[i][2 * h + j] = MF::mma(fb[h][j][ks], fa[i][ks], acc[i][2 * h + j]);
-      __builtin_amdgcn_s_setprio(0);
       barrier();
     };
     using I0 = std::integral_constant<int, 0>;
