@@ -154,11 +154,9 @@ __device__ __forceinline__ void store_pair(bf16* p, u32x4 v, int col, int N, boo
   }
 }
 
-// MFMA shapes per tile family: the compute-bound prefill tiles (256 x 256,
-// the grouped expert tiles of 128 or 256 rows) and the mid-size-M tiles.  The
+// MFMA shape of the large tiles (256 x 256, 128 x 256, 128 x 128).  The
 // weight-streaming decode tiles keep 32 x 32 blocks.
-constexpr int kPrefillSH = 16;
-constexpr int kMidSH = 16;
+constexpr int kTileSH = 16;
 
 template <int BM, int BN, int S = 2>
 struct GemmSmem {
@@ -364,14 +362,14 @@ struct Mainloop {
                                                    __amdgpu_buffer_rsrc_t rb,
                                                    const uint32_t (&b_off)[B_BLK], int K, int wv,
                                                    int lane, acc_t (&acc)[MI][NI],
-                                                   const ResPf& rp = ResPf{}, int kshift = 0) {
+                                                   int kshift = 0) {
     const int wm = wv / WGN;
     const int act = (rows - wm * WM + SH - 1) / SH;  // row blocks holding valid rows
     if constexpr (MA == 0) {
       run_rows<0>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
     } else {
       if (act >= MA) run_rows<MA>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
-      else run_valid<MA - 1>(rows, sm, ra, a_off, rb, b_off, K, wv, lane, acc, rp, kshift);
+      else run_valid<MA - 1>(rows, sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
     }
   }
 };
@@ -596,7 +594,7 @@ struct PingLoop : PingCols<2> {
                                                    __amdgpu_buffer_rsrc_t rb,
                                                    const uint32_t (&b_off)[B_BLK], int K, int wv,
                                                    int lane, acc_t (&acc)[MI][NI],
-                                                   const ResPf& rp = ResPf{}, int kshift = 0) {
+                                                   int kshift = 0, const ResPf& rp = ResPf{}) {
     const int wm = wv >> 2;
     const int c0 = (rows - wm * 64 + SH - 1) / SH;        // blocks of the first half
     const int c1 = (rows - 128 - wm * 64 + SH - 1) / SH;  // of the second
@@ -755,7 +753,7 @@ struct PingSmall : PingCols<HB> {
                                                    __amdgpu_buffer_rsrc_t rb,
                                                    const uint32_t (&b_off)[B_BLK], int K, int wv,
                                                    int lane, acc_t (&acc)[MI][NI],
-                                                   const ResPf& = ResPf{}, int kshift = 0) {
+                                                   int kshift = 0) {
     const int c = (rows - (wv >> 2) * 64 + SH - 1) / SH;
     if (c > 2) run_rows<4>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
     else if (c > 1) run_rows<2>(sm, ra, a_off, rb, b_off, K, wv, lane, acc, kshift);
@@ -1251,7 +1249,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_kernel(const bf16* __r
   }
   if constexpr (PP && BM == 256)
     ML::template run_valid<kResPf>(M - tm * BM, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc,
-                                   rp);
+                                   0, rp);
   else
     ML::run_valid(M - tm * BM, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc);
   // the wave's first column within the tile, and its second half's distance
@@ -1379,7 +1377,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_grouped_kernel(
   // tiles of one expert share their k-slices in L2, does not.
   const bool rotate = BM <= 32 || KIND == EPI_STORE_F32;
   const int kshift = rotate ? (int)(((unsigned)id * 7u) % (unsigned)(K / kBK)) : 0;
-  ML::run_valid(p_end - p0, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc, ResPf{}, kshift);
+  ML::run_valid(p_end - p0, sm, rsrc_a, a_off, rsrc_b, b_off, K, wv, lane, acc, kshift);
 
   const int lr = Geo::lane_row(lane), lc = Geo::lane_col(lane);
   const int row0 = p0 + wm * WM + lr;
@@ -1613,9 +1611,9 @@ static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, 
       }
       const size_t hsmem = sizeof(GemmSmem<128, 256, 3>);
       static bool half_attr = false;
-      e = opt_in_lds(gemm_kernel<128, 256, 2, 4, EK, 3, kMidSH>, hsmem, half_attr);
+      e = opt_in_lds(gemm_kernel<128, 256, 2, 4, EK, 3, kTileSH>, hsmem, half_attr);
       if (e != hipSuccess) return e;
-      gemm_kernel<128, 256, 2, 4, EK, 3, kMidSH><<<2 * n_tail, 512, hsmem, s>>>(
+      gemm_kernel<128, 256, 2, 4, EK, 3, kTileSH><<<2 * n_tail, 512, hsmem, s>>>(
           (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, K, epi, tiles_m, tiles_n, full, 0,
           nullptr);
       return hipGetLastError();
@@ -1641,11 +1639,11 @@ static hipError_t run_planned(const void* A, int lda, const void* B, int ldb, in
   const GemmPlan p = gemm_plan(M, KIND == EPI_SWIGLU ? 2 * epi.ffn : N, K, KIND == EPI_SWIGLU,
                                tail != nullptr, epi.routed != 0, cu_count());
   if (p.bm == 256)
-    return run_gemm_tail<256, 256, 2, 4, EK, 2, kPrefillSH>(A, lda, B, ldb, M, N, K, epi, tail, s,
+    return run_gemm_tail<256, 256, 2, 4, EK, 2, kTileSH>(A, lda, B, ldb, M, N, K, epi, tail, s,
                                                             p.split);
   if (p.bn == 256)
-    return run_gemm<128, 256, 2, 4, EK, 3, kMidSH>(A, lda, B, ldb, M, N, K, epi, s);
-  return run_gemm_tail<128, 128, 2, 4, EK, 5, kMidSH>(A, lda, B, ldb, M, N, K, epi, tail, s, p.split);
+    return run_gemm<128, 256, 2, 4, EK, 3, kTileSH>(A, lda, B, ldb, M, N, K, epi, s);
+  return run_gemm_tail<128, 128, 2, 4, EK, 5, kTileSH>(A, lda, B, ldb, M, N, K, epi, tail, s, p.split);
 }
 
 hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
@@ -1703,9 +1701,9 @@ hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t
       return run_grouped<32, 256, 1, 4, EK>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
                                             tile_off, n_experts, max_tiles_m, epi, s);
     if (bm == 256)
-      return run_grouped<256, 256, 2, 4, EK, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
+      return run_grouped<256, 256, 2, 4, EK, kTileSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
                                              tile_off, n_experts, max_tiles_m, epi, s);
-    return run_grouped<128, 256, 2, 4, EK, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
+    return run_grouped<128, 256, 2, 4, EK, kTileSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K, seg,
                                            tile_off, n_experts, max_tiles_m, epi, s);
   }
   if (bm == 32) {
@@ -1717,16 +1715,16 @@ hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t
   }
   if (bm == 256) {
     if (epi.kind == EPI_SWIGLU)
-      return run_grouped<256, 256, 2, 4, EPI_SWIGLU, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
+      return run_grouped<256, 256, 2, 4, EPI_SWIGLU, kTileSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
                                                       seg, tile_off, n_experts, max_tiles_m, epi, s);
-    return run_grouped<256, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N,
+    return run_grouped<256, 256, 2, 4, EPI_STORE_F32, kTileSH>(A, lda, a_rows, perm, top_k, B, b_stride, N,
                                                        K, seg, tile_off, n_experts, max_tiles_m, epi,
                                                        s);
   }
   if (epi.kind == EPI_SWIGLU)
-    return run_grouped<128, 256, 2, 4, EPI_SWIGLU, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
+    return run_grouped<128, 256, 2, 4, EPI_SWIGLU, kTileSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
                                                     seg, tile_off, n_experts, max_tiles_m, epi, s);
-  return run_grouped<128, 256, 2, 4, EPI_STORE_F32, kPrefillSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
+  return run_grouped<128, 256, 2, 4, EPI_STORE_F32, kTileSH>(A, lda, a_rows, perm, top_k, B, b_stride, N, K,
                                                      seg, tile_off, n_experts, max_tiles_m, epi, s);
 }
 
