@@ -116,21 +116,23 @@ tri_status tri_layer_work(const tri_layer_config* cfg, int32_t decode, int32_t n
     a.add(ST_ATTN_COMBINE, 2.0 * dec_parts * Hq * D, part_elems * f32 + dec_tok * Hq * D * bf);
   }
 
-  // O projection + residual, then RMSNorm(x1; mlp_norm) -- one stage for a
-  // short batch, whose split-K reduction applies the norm (x1 then never
-  // re-read).
+  // O projection + residual, then RMSNorm(x1; mlp_norm): with gate/up for a
+  // dense layer's few rows, with O for a short batch, whose split-K reduction
+  // applies it (x1 then never re-read), else a stage of its own.
   const double o_flops = 2.0 * T * H * Hq * D, o_bytes = H * Hq * D * bf + T * Hq * D * bf +
                                                          2.0 * T * H * bf;
-  if (skinny_resid_norm_fused((int)T, cfg->hidden, cfg->n_q_heads * cfg->head_dim)) {
-    a.add(ST_OPROJ, o_flops + 4.0 * T * H, o_bytes + T * H * bf + H * bf);
-  } else {
-    a.add(ST_OPROJ, o_flops, o_bytes);
-    a.add(ST_NORM2, 4.0 * T * H, 2.0 * T * H * bf + H * bf);
-  }
+  const double norm_flops = 4.0 * T * H, norm_bytes = T * H * bf + H * bf;  // h2, gains
+  const bool norm_in_gate_up = !moe && stream_norm_ok((int)T, cfg->hidden);
+  const bool norm_in_o =
+      !norm_in_gate_up &&
+      skinny_resid_norm_fused((int)T, cfg->hidden, cfg->n_q_heads * cfg->head_dim);
+  a.add(ST_OPROJ, o_flops + (norm_in_o ? norm_flops : 0.0), o_bytes + (norm_in_o ? norm_bytes : 0.0));
+  if (!norm_in_gate_up && !norm_in_o) a.add(ST_NORM2, norm_flops, norm_bytes + T * H * bf);
 
   if (!moe) {
     const double F = cfg->ffn_dim;
-    a.add(ST_GATEUP, 2.0 * T * 2.0 * F * H, 2.0 * F * H * bf + T * H * bf + T * F * bf);
+    a.add(ST_GATEUP, 2.0 * T * 2.0 * F * H + (norm_in_gate_up ? norm_flops : 0.0),
+          2.0 * F * H * bf + T * H * bf + T * F * bf + (norm_in_gate_up ? norm_bytes : 0.0));
     a.add(ST_DOWN, 2.0 * T * H * F, H * F * bf + T * F * bf + 2.0 * T * H * bf);
     return TRI_OK;
   }

@@ -95,6 +95,27 @@ def test_dense_decode_bytes(lib):
     assert total(w, "flops") == pytest.approx(33.6e9, rel=5e-3)
 
 
+def test_the_second_norm_is_counted_where_it_runs(lib):
+    """RMSNorm(x1): 4 H flops a token, h2 written and the gains read; with
+    gate/up up to four tokens of 3584, with O up to 128, a stage of its own
+    beyond, which reads x1 too."""
+    from synth import Batch
+    H, F = 3584, 18944
+    for n, where in ((1, "gate_up"), (4, "gate_up"), (5, "o_proj"), (128, "o_proj"),
+                     (200, "rmsnorm_mlp")):
+        b = Batch(np.arange(n, dtype=np.int32), 100 * np.ones(n, np.int32), np.ones(n, np.int32))
+        s = stages(work("dense_decode", decode=True, batch=b))
+        plain = {"o_proj": (2 * n * H * H, 2 * (H * H + 3 * n * H)),
+                 "gate_up": (4 * n * F * H, 2 * (2 * F * H + n * H + n * F)),
+                 "rmsnorm_mlp": (0, 2 * n * H)}
+        norm = 4 * n * H, 2 * (n * H + H)
+        assert ("rmsnorm_mlp" in s) == (where == "rmsnorm_mlp")
+        for k in plain:
+            if k in s:
+                want = [p + q * (k == where) for p, q in zip(plain[k], norm)]
+                assert [s[k]["flops"], s[k]["bytes"]] == want, (n, k)
+
+
 def test_decode_attention_intensity_is_the_group_size(lib):
     # Every K/V byte serves Hq / Hkv query heads with 2 flops per multiply-add
     # over two products: flops / bytes -> Hq / Hkv as the KV dominates.
