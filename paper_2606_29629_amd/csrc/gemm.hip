@@ -1415,10 +1415,6 @@ static hipError_t run_gemm(const void* A, int lda, const void* B, int ldb, int M
   return hipGetLastError();
 }
 
-// Tail split of a large GEMM: with 256 x 256 tiles, one workgroup per CU,
-// the last (tiles % CUs) tiles -- all of them when there are fewer tiles than
-// CUs -- would run as a partial round; split into `tsplit` K-parts they fill
-// it.
 int cu_count() {
   static int n = 0;
   if (n == 0) {
@@ -1584,6 +1580,8 @@ __global__ __launch_bounds__(256) void tail_epi_kernel(const float* __restrict__
   }
 }
 
+// A GEMM whose last partial round of tiles (tail_tiles), one workgroup per CU, is
+// cut in `t` K-parts (t > 1) or 128-row halves (t = 0) that fill it.
 template <int BM, int BN, int WGM, int WGN, int EK, int S, int SH>
 static hipError_t run_gemm_tail(const void* A, int lda, const void* B, int ldb, int M, int N,
                                 int K, const Epi& epi, float* tail, hipStream_t s, int t) {

@@ -22,7 +22,8 @@
 // + norm -> 8 us, the step 131 -> 110 us; the Talker's step 50 -> 34 us.
 // Beyond 16 tokens the activations become a stream as large as the weights'
 // (23 tokens: down 32 -> 38 us, 64 tokens: gate/up 62 -> 78 us), and the
-// workgroup-wide 64-row tiles of the skinny GEMM are faster.
+// workgroup-wide 64-row tiles of the skinny GEMM are faster; so they are, with
+// fewer tokens, for a narrow matrix with a long K (stream_rows).
 #include "common.hpp"
 #include "kernels.hpp"
 
