@@ -429,13 +429,14 @@ struct PingCols {
 // read six phases after its load was issued; the wait of the phase before
 // leaves the five newer half tiles' ten loads in flight.
 //
-// What bounds it: the board's power.  A loop with one barrier per k-tile has to
-// issue a k-tile's loads in one burst once the whole buffer is free, so a
-// k-tile took the burst plus a memory round trip (3060 clocks for 2048 of
-// MFMAs); here loads are issued at an even rate and each group's MFMAs cover
-// the other's LDS reads (2450 clocks).  8192^3: 819 -> 755 us on random
-// operands (1343 -> 1455 TFLOP/s), 677 -> 593 us on zeros, which draw less
-// power; gate/up at 16384 x 3584 (SwiGLU) 3380 -> 3083 us, down 1720 -> 1671 us.
+// What bounds it: the board's power (gate/up at 16384 x 3584: the MFMA pipes are
+// busy for 84% of the cycles, and the clock is held at 1.8 of 2.4 GHz).  A loop
+// with one barrier per k-tile has to issue a k-tile's loads in one burst once
+// the whole buffer is free, so a k-tile took the burst plus a memory round trip
+// (3060 clocks for 2048 of MFMAs); here loads are issued at an even rate and each
+// group's MFMAs cover the other's LDS reads (2450 clocks).  8192^3: 819 -> 755 us
+// on random operands (1343 -> 1455 TFLOP/s), 677 -> 593 us on zeros, which draw
+// less power; gate/up at 16384 x 3584 (SwiGLU) 3380 -> 3083 us, down 1720 -> 1671 us.
 // Without the stagger of the groups 868 us; loads issued between the MFMAs
 // 840 us; a raised wave priority around the MFMAs (8 x 2048 prefill 5950 with it,
 // 5935 us without), the order of reads and loads in a phase and the order of the
@@ -618,7 +619,8 @@ struct PingLoop : PingCols<2> {
 // loaded again from the next phase on: the four (three) youngest phases'
 // loads, up to 96 KB per CU, stay in flight.
 // What bounds it: one k-tile's loads (32 or 48 KB) take as long from L2 as its
-// MFMAs.  The four- and eight-wave loops with one barrier per k-tile that
+// MFMAs (ragged prefill of 1061 tokens: waves wait for 34 to 44% of their cycles,
+// 4 to 6% on LDS).  The four- and eight-wave loops with one barrier per k-tile that
 // these replace waited for LDS and for each load burst instead.
 template <int HB>
 struct PingSmall : PingCols<HB> {
