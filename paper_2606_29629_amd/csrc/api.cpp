@@ -221,11 +221,11 @@ Layout layout_of(const tri_layer_config* c, const tri_batch* b) {
   l.seg = o;      o += up((E + 1) * 4);
   l.tile_off = o; o += up((E + 1) * 4);
   l.y = o;        o += up(P * H * 4);
-  // Router logit planes [S][T][E]: S * T <= max(T, 51200 / ceil(E / 64)) for
+  // Router logit planes [S][T][plane_ld(E)]: S * T <= max(T, 51200 / ceil(E / 64)) for
   // every split count the GEMM picks (S > 1 only while S * tiles < 800), a
   // bound that never decreases with T.
   const size_t rows = moe ? std::max(T, (size_t)51200 / ((E + 63) / 64)) : 0;
-  l.logits = o;   o += up(rows * E * 4);
+  l.logits = o;   o += up(rows * plane_ld((int)E) * 4);
   l.total = o;
   return l;
 }

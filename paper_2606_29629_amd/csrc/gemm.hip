@@ -2043,7 +2043,7 @@ hipError_t launch_gemm_planes(const void* A, int lda, const void* B, int ldb, in
   Epi pe{};
   pe.kind = EPI_STORE_F32;
   pe.out = planes;
-  pe.ldo = N;
+  pe.ldo = plane_ld(N);
   return run_gemm<64, kSkinnyBN, 2, 1, EPI_STORE_F32>(A, lda, B, ldb, M, N, K, pe, s, splits);
 }
 

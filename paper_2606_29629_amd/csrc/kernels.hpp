@@ -126,8 +126,8 @@ size_t gemm_tail_bytes();
 hipError_t launch_gemm(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                        const Epi& epi, float* tail, hipStream_t s);
 
-// fp32 C = A B^T as split-K planes [splits][M][N] (the consumer sums them
-// in plane order); gemm_planes_splits picks the split count.
+// fp32 C = A B^T as split-K planes [splits][M][plane_ld(N)] (the consumer sums
+// them in plane order); gemm_planes_splits picks the split count.
 int gemm_planes_splits(int M, int N, int K);
 hipError_t launch_gemm_planes(const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                               float* planes, int splits, hipStream_t s);
@@ -208,7 +208,6 @@ hipError_t launch_gemm_grouped(const void* A, int lda, int a_rows, const int32_t
 hipError_t launch_moe_route_f32(const float* h32, const void* w_router, int T, int H, int E,
                                 int k, int renorm, int32_t* idx, float* w, hipStream_t s,
                                 bool w_f32 = false);
-size_t moe_route_planes_bytes(int T, int H, int E);
 hipError_t launch_moe_route_bf16(const void* h, const void* w_router, int T, int H, int E, int k,
                                  int renorm, float* planes, int32_t* idx, float* w, hipStream_t s);
 hipError_t launch_moe_permute(const int32_t* idx, int n_pairs, int E, int bm, int32_t* rank,

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void moe_router_kernel(const InT* __restrict__
 }
 
 // Router on the matrix cores: the logits arrive as split-K planes
-// [S][T][E] (fp32, from a bf16 GEMM of h2 and W_r with fp32 accumulation);
+// [S][T][plane_ld(E)] (fp32, from a bf16 GEMM of h2 and W_r with fp32 accumulation);
 // they are summed in plane order (deterministic) before top-k.  One wave per
 // token.
 __global__ __launch_bounds__(256) void moe_topk_kernel(const float* __restrict__ planes, int S,
@@ -183,8 +183,8 @@ __global__ __launch_bounds__(256) void moe_topk_kernel(const float* __restrict__
   // Every plane's value is loaded before the ordered sum (S <= kMaxPlanes),
   // so the loads are in flight together; planes past S and experts past E
   // re-read an in-range address and are dropped.
-  const float* base = planes + (int64_t)t * E;
-  const int64_t plane = (int64_t)T * E;
+  const float* base = planes + (int64_t)t * plane_ld(E);
+  const int64_t plane = (int64_t)T * plane_ld(E);
   float pv[4][kMaxPlanes];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -216,10 +216,6 @@ hipError_t launch_moe_route_f32(const float* h32, const void* w_router, int T, i
     moe_router_kernel<float><<<cdiv(T, kRouteTok), 256, 0, s>>>(h32, (const bf16*)w_router, T, H,
                                                                  E, k, renorm, idx, w);
   return hipGetLastError();
-}
-
-size_t moe_route_planes_bytes(int T, int H, int E) {
-  return (size_t)gemm_planes_splits(T, E, H) * T * E * sizeof(float);
 }
 
 hipError_t launch_moe_route_bf16(const void* h, const void* w_router, int T, int H, int E, int k,

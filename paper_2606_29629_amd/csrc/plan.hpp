@@ -12,6 +12,10 @@ constexpr int kBK = 64;  // k per GEMM k-tile
 
 constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 
+// Row stride of fp32 planes with N columns: the epilogues write columns in
+// groups of four.
+constexpr int plane_ld(int N) { return cdiv(N, 4) * 4; }
+
 // Tiles of the final partial round: total % CUs, or all of them when the
 // GEMM has fewer tiles than CUs.
 constexpr int tail_tiles(int total, int G) {

@@ -427,3 +427,17 @@ def test_workspace_holds_the_plane_of_a_normed_qkv_of_few_tokens(lib):
                 plane = 4 * n * (c.n_q_heads + 2 * c.n_kv_heads) * 64
                 act_end = m.act + -(-2 * n * c.ffn_dim // 256) * 256
                 assert m.total - act_end >= plane, (c.hidden, n, m.total - act_end, plane)
+
+
+def test_workspace_holds_the_router_logits_of_any_expert_count(lib):
+    """Logit rows are written in groups of four columns: the last workspace
+    region (after y) holds rows of E rounded up to four, also for one plane of
+    a long prompt."""
+    for E, n in ((17, 65536), (3, 51200), (255, 65536), (64, 65536)):
+        c = cfg(hidden=64, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=0, n_experts=E, top_k=1,
+                expert_ffn_dim=64, flags=T.TRI_F_MOE)
+        b = batch(n_seqs=1, n_tokens=n, max_q=n, max_ctx=0)
+        m = T.WorkspaceMap()
+        assert lib.tri_workspace_layout(ctypes.byref(c), ctypes.byref(b), ctypes.byref(m)) == 0
+        y_end = m.y + -(-4 * n * 64 // 256) * 256
+        assert m.total - y_end >= 4 * n * (-(-E // 4) * 4)
