@@ -35,7 +35,7 @@ constexpr int kMaxTailSplit = 8;  // K-parts of a tail tile, at most
 // 256 0.74 us, 128 x 128 0.60 us).  Waiting for a k-tile's loads (64, 48, 32 KB)
 // sets them, not LDS: in the ragged and the mixed prefill the waves of these forms
 // wait for 26 to 44% of their cycles, LDS is active for 15 to 30% of the CUs' and the
-// MFMA pipes for 19 to 67%, and the K-parts of down draw 6.3 TB/s from beyond L2.
+// MFMA pipes for 19 to 67%, and the K-parts of down draw 6 to 7 TB/s from beyond L2.
 // The largest tile does the most per byte, so the small ones only pay where they
 // fill more of the CUs.
 struct GemmPlan {
